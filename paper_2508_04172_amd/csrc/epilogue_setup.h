@@ -114,4 +114,82 @@ __device__ __forceinline__ double lnl_weight(const int4 d, const EpiSetup &o, in
   return rr * rr * (ara * aib - aia * arb);
 }
 
+// The setups of `cnt` (at most 64) proposals g0 .. g0 + cnt - 1 by one
+// workgroup of four waves, the same arithmetic as epi_setup item by item:
+// wave 0 the domain checks (a lane per proposal), wave 1 the detector
+// responses and stencils (a lane per proposal and detector), waves 2 and 3
+// the harmonics (a lane per proposal, mode and sign), then every thread the
+// amplitudes.  A lane of epi_setup walks about 25 sines, cosines and powers in
+// a row; split this way the longest chain is one item of each kind, which is
+// what a small batch waits for.  consts(j): the constants of the j-th
+// proposal's event; ylm(j, i): its harmonic terms, i < n_modes of -m, then of
+// +m; nd, nm: bounds of its detector and mode counts.  Ends with a block
+// barrier.
+struct EpiTmp {
+  double fp[RBFL_MAX_DET], fc[RBFL_MAX_DET];
+  double yr[2 * RBFL_MAX_MODES], yi[2 * RBFL_MAX_MODES];
+  int pre, out[RBFL_MAX_DET];
+};
+
+template <class ConstsOf, class YlmOf>
+__device__ __forceinline__ void epi_setup_block(ConstsOf consts, YlmOf ylm, int nd, int nm,
+                                                const double *__restrict__ params, int64_t ld, int64_t g0, int cnt,
+                                                EpiSetup *su, EpiTmp *tmp) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (wave == 0) {
+    if (lane < cnt) {
+      const EvalConsts &c = consts(lane);
+      double p[11];
+      tmp[lane].pre = epi_prelude(c, params, ld, g0 + lane, p);
+      su[lane].rr = c.d_ref / p[10];
+    }
+  } else if (wave == 1) {
+    for (int e = lane; e < cnt * nd; e += 64) {
+      const int j = e / nd, k = e - j * nd;
+      const EvalConsts &c = consts(j);
+      if (k >= c.n_det) continue;
+      const int64_t g = g0 + j;
+      double fp, fc, dt;
+      detector_response(c.D[k], c.r[k], params[4 * ld + g], params[5 * ld + g], params[6 * ld + g], &fp, &fc, &dt);
+      const double s = (params[9 * ld + g] + dt - c.t_trig) * c.fs + (double)c.half_w;
+      const double fl = floor(s);
+      const bool in = fl >= 4.0 && fl <= (double)(c.T - 6);
+      su[j].n0[k] = in ? (int)fl : 4;
+      su[j].f[k] = s - fl;
+      tmp[j].fp[k] = fp;
+      tmp[j].fc[k] = fc;
+      tmp[j].out[k] = in ? 0 : 1;
+    }
+  } else {
+    for (int e = (wave - 2) * 64 + lane; e < cnt * 2 * nm; e += 128) {
+      const int j = e / (2 * nm), i = e - j * 2 * nm;
+      if (i >= 2 * consts(j).n_modes) continue;
+      const int64_t g = g0 + j;
+      double ch, sh;
+      sincos(0.5 * params[7 * ld + g], &sh, &ch);
+      eval_ylm(ylm(j, i), ch, sh, params[8 * ld + g], &tmp[j].yr[i], &tmp[j].yi[i]);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < cnt * nd * nm; e += 256) {
+    const int j = e / (nd * nm), r = e - j * nd * nm, k = r / nm, a = r - k * nm;
+    const EvalConsts &c = consts(j);
+    const int n = c.n_modes;
+    if (k >= c.n_det || a >= n) continue;
+    const double fp = tmp[j].fp[k], fc = tmp[j].fc[k];
+    const double ynr = tmp[j].yr[a], yni = tmp[j].yi[a], ypr = tmp[j].yr[n + a], ypi = tmp[j].yi[n + a];
+    const double sg = (c.mode_l[a] & 1) ? -1.0 : 1.0;
+    su[j].Ar[k][a] = 0.5 * ((fp * ynr - fc * yni) + sg * (fp * ypr - fc * ypi));
+    su[j].Ai[k][a] = 0.5 * ((fp * yni + fc * ynr) + sg * (-fp * ypi - fc * ypr));
+  }
+  if ((int)threadIdx.x < cnt) {
+    const int j = threadIdx.x;
+    int bad = tmp[j].pre;
+    if (bad == 0)
+      for (int k = 0; k < consts(j).n_det; ++k) bad |= tmp[j].out[k];
+    su[j].status = bad;
+  }
+  __syncthreads();
+}
+
 }  // namespace rbfl

@@ -205,27 +205,24 @@ __global__ void __launch_bounds__(kThreads) k_contract_fp32(const EvalConsts *__
   }
 }
 
-// The epilogue runs in two phases per block of kEpiBatch proposals.
+// The epilogue runs in two phases per workgroup of EB proposals.
 //
-// Setup (one lane per proposal): the proposal's domain flags (inside the
-// ellipsoid, physical, every detector's spline stencil inside the window, no
-// NaN input), each detector's arrival-time position (stencil base and
-// fraction), each (detector, mode) amplitude A_{k,lm} =
+// Setup (epi_setup_block): the proposals' domain flags (inside the ellipsoid,
+// physical, every detector's spline stencil inside the window, no NaN input),
+// each detector's arrival-time position (stencil base and fraction), each
+// (detector, mode) amplitude A_{k,lm} =
 // [(F+ + iFx) Y_{l,-m} + (-1)^l (F+ - iFx) conj(Y_lm)] / 2 (Eq. logl_complete,
-// corrected reading) and d_ref / d_L, into LDS.  These need transcendental
-// functions but not the interpolated coefficients, so a lane per proposal
-// does them once instead of a wave per proposal.
+// corrected reading) and d_ref / d_L, into LDS.
 //
 // Reduction (one wave per proposal): the lanes are split over the (detector,
 // mode) pairs -- G = 64 / (n_det * n_modes) lanes per pair -- and each pair's
 // lanes stride over its q basis coefficients: lane g of pair (k, a)
 // accumulates sum_i C_i sum_p f^p B4[n0][i][p] over i = g, g+G, ... with the
 // spline-folded basis B4 (the entries of one row are contiguous in i, so the
-// G lanes of a pair read adjacent 64-byte groups).  Partial sums meet in the pair's first lane by shuffles; that lane
-// forms Re(conj(A) z), the detector's first lane the overlap term, lane 0 the
-// sum, all with compensated (Neumaier) additions.
-constexpr int kEpiBatch = 64;
-static_assert(kEpiBatch + RBFL_MAX_DET * RBFL_MAX_MODES <= kThreads, "offset copy threads");
+// G lanes of a pair read adjacent 64-byte groups).  Partial sums meet in the
+// pair's first lane by shuffles; that lane forms Re(conj(A) z), the detector's
+// first lane the overlap term, lane 0 the sum, all with compensated (Neumaier)
+// additions.
 
 // ln L of one proposal from its setup o and interpolated row y; one whole
 // wave per call, result written to *out by lane 0.  The loads of each stage
@@ -236,6 +233,7 @@ constexpr int kEpiUnroll = 2;
 
 // coef_off / sig_off: the output offsets of the consts (an LDS copy where the
 // block has one).
+template <int U = kEpiUnroll>
 __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &o, const double *__restrict__ y,
                                            const double2 *__restrict__ basis4, double *__restrict__ out,
                                            const int (*coef_off)[RBFL_MAX_MODES], const int *sig_off) {
@@ -279,10 +277,10 @@ __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &
   if (active) {
     const int off = coef_off[k][a];
     const double2 *base = basis4 + ((int64_t)(k * n_modes + a) * T + n0) * q * 4;
-    for (int i0 = gl; i0 < q; i0 += kEpiUnroll * G) {
-      double2 cc[kEpiUnroll], v[kEpiUnroll][4];
+    for (int i0 = gl; i0 < q; i0 += U * G) {
+      double2 cc[U], v[U][4];
 #pragma unroll
-      for (int u = 0; u < kEpiUnroll; ++u) {
+      for (int u = 0; u < U; ++u) {
         // past the end: a valid entry is loaded and its coefficient zeroed,
         // so that every load is issued before the first use
         const bool ok = i0 + u * G < q;
@@ -294,7 +292,7 @@ __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &
         for (int j = 0; j < 4; ++j) v[u][j] = base[4 * i + j];
       }
 #pragma unroll
-      for (int u = 0; u < kEpiUnroll; ++u) {
+      for (int u = 0; u < U; ++u) {
         const double br = fma(fma(fma(v[u][3].x, f, v[u][2].x), f, v[u][1].x), f, v[u][0].x);
         const double bi = fma(fma(fma(v[u][3].y, f, v[u][2].y), f, v[u][1].y), f, v[u][0].y);
         zr += cc[u].x * br - cc[u].y * bi;
@@ -302,12 +300,16 @@ __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &
       }
     }
   }
-  // combine the G partials of each pair in its first lane (fixed order)
-  const int lead = pair * G;
-  double tr = 0.0, ti = 0.0;
-  for (int j = 0; j < G; ++j) {
-    tr += __shfl(zr, lead + j, 64);
-    ti += __shfl(zi, lead + j, 64);
+  // combine the G partials of each pair in its first lane (a fixed tree: after
+  // the step of distance o, lane g of a pair holds the sum over lanes
+  // g .. g + 2 o - 1 of it)
+  double tr = zr, ti = zi;
+  for (int o = 1; o < G; o <<= 1) {
+    const double vr = __shfl(tr, lane + o, 64), vi = __shfl(ti, lane + o, 64);
+    if (gl + o < G) {
+      tr += vr;
+      ti += vi;
+    }
   }
   const double zterm = ar * tr + ai * ti;   // Re(conj(A) z), valid in pair leaders
   // overlap term of detector k: every A_{k,b} is in the setup
@@ -344,26 +346,37 @@ __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &
   if (lane == 0) *out = tot + comp;
 }
 
+// EB proposals per workgroup, U coefficients in flight per lane.
+template <int EB, int U>
 __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restrict__ cp,
                                                        const double *__restrict__ params, int64_t ld, int64_t b0,
                                                        int64_t nb, const double *__restrict__ Y,
                                                        const double2 *__restrict__ basis4, double *__restrict__ lnl) {
-  __shared__ EpiSetup su[kEpiBatch];
+  __shared__ EpiSetup su[EB];
+  __shared__ EpiTmp tmp[EB];
+  __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
   __shared__ int coef_off[RBFL_MAX_DET][RBFL_MAX_MODES], sig_off[RBFL_MAX_DET];
   const EvalConsts &c = *cp;
-  const int64_t first = (int64_t)blockIdx.x * kEpiBatch;
-  if (threadIdx.x < kEpiBatch && first + threadIdx.x < nb) epi_setup(c, params, ld, b0 + first + threadIdx.x, su[threadIdx.x]);
-  if (threadIdx.x >= kEpiBatch && threadIdx.x < kEpiBatch + RBFL_MAX_DET * RBFL_MAX_MODES) {
-    const int e = threadIdx.x - kEpiBatch;
+  const int64_t first = (int64_t)blockIdx.x * EB;
+  const int cnt = (int)(nb - first < EB ? nb - first : EB);
+  // the harmonics' terms, word by word: n_modes of -m, then n_modes of +m
+  constexpr int kWords = sizeof(YlmTerms) / 4;
+  static_assert(sizeof(YlmTerms) % 4 == 0, "copied by words");
+  const int words = c.n_modes * kWords;
+  for (int e = threadIdx.x; e < 2 * words; e += kThreads)
+    reinterpret_cast<int *>(ylm)[e] =
+        e < words ? reinterpret_cast<const int *>(c.ylm_neg)[e] : reinterpret_cast<const int *>(c.ylm_pos)[e - words];
+  if (threadIdx.x < RBFL_MAX_DET * RBFL_MAX_MODES) {
+    const int e = threadIdx.x;
     coef_off[e / RBFL_MAX_MODES][e % RBFL_MAX_MODES] = c.coef_off[e / RBFL_MAX_MODES][e % RBFL_MAX_MODES];
     if (e < RBFL_MAX_DET) sig_off[e] = c.sig_off[e];
   }
   __syncthreads();
-  for (int j = threadIdx.x >> 6; j < kEpiBatch; j += kWaves) {
-    const int64_t b = first + j;
-    if (b >= nb) break;   // whole wave leaves together
-    epi_reduce(c, su[j], Y + b * c.Kp, basis4, lnl + b0 + b, coef_off, sig_off);
-  }
+  const int nm = c.n_modes;
+  epi_setup_block([&](int) -> const EvalConsts & { return c; }, [&](int, int i) -> const YlmTerms & { return ylm[i]; },
+                  c.n_det, nm, params, ld, b0 + first, cnt, su, tmp);
+  for (int j = threadIdx.x >> 6; j < cnt; j += kWaves)
+    epi_reduce<U>(c, su[j], Y + (first + j) * c.Kp, basis4, lnl + b0 + first + j, coef_off, sig_off);
 }
 
 // Epilogue of the time-banded form (n_bands = B > 1): one wave per proposal,
@@ -582,14 +595,17 @@ __global__ void k_zero_counter(unsigned long long *counter) {
 }
 
 // The epilogue's two phases over the concatenated batch; each proposal's
-// event is found in the setup phase by binary search over the events' first
-// proposals (caller order).
+// event is found first, by binary search over the events' first proposals
+// (caller order).
+template <int EB>
 __global__ void __launch_bounds__(kThreads) k_ragged_epilogue(const EventDesc *__restrict__ ev, int n_ev,
                                                               const double *__restrict__ params, int64_t total,
                                                               double *__restrict__ lnl) {
-  __shared__ EpiSetup su[kEpiBatch];
-  const int64_t first = (int64_t)blockIdx.x * kEpiBatch;
-  if (threadIdx.x < kEpiBatch && first + threadIdx.x < total) {
+  __shared__ EpiSetup su[EB];
+  __shared__ EpiTmp tmp[EB];
+  const int64_t first = (int64_t)blockIdx.x * EB;
+  const int cnt = (int)(total - first < EB ? total - first : EB);
+  if ((int)threadIdx.x < cnt) {
     const int64_t g = first + threadIdx.x;
     int lo = 0, hi = n_ev - 1;
     while (lo < hi) {
@@ -597,15 +613,19 @@ __global__ void __launch_bounds__(kThreads) k_ragged_epilogue(const EventDesc *_
       if (ev[mid].q0 <= g) lo = mid;
       else hi = mid - 1;
     }
-    epi_setup(*ev[lo].consts, params, total, g, su[threadIdx.x]);
     su[threadIdx.x].event = lo;
   }
   __syncthreads();
-  for (int j = threadIdx.x >> 6; j < kEpiBatch; j += kWaves) {
+  epi_setup_block([&](int j) -> const EvalConsts & { return *ev[su[j].event].consts; },
+                  [&](int j, int i) -> const YlmTerms & {
+                    const EvalConsts &c = *ev[su[j].event].consts;
+                    return i < c.n_modes ? c.ylm_neg[i] : c.ylm_pos[i - c.n_modes];
+                  },
+                  RBFL_MAX_DET, RBFL_MAX_MODES, params, total, first, cnt, su, tmp);
+  for (int j = threadIdx.x >> 6; j < cnt; j += kWaves) {
     const int64_t g = first + j;
-    if (g >= total) break;   // whole wave leaves together
     const EventDesc &d = ev[su[j].event];
-    epi_reduce(*d.consts, su[j], d.Y + (g - d.q0) * d.Kp, d.basis, lnl + g, d.consts->coef_off, d.consts->sig_off);
+    epi_reduce<>(*d.consts, su[j], d.Y + (g - d.q0) * d.Kp, d.basis, lnl + g, d.consts->coef_off, d.consts->sig_off);
   }
 }
 
@@ -798,9 +818,32 @@ void launch_ragged_contract(int variant, const EventDesc *ev, int n_ev, int64_t 
 
 void launch_ragged_epilogue(const EventDesc *ev, int n_ev, const double *params, int64_t total, double *lnl,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_ragged_epilogue, dim3((unsigned)((total + kEpiBatch - 1) / kEpiBatch)), dim3(kThreads), 0, s,
-                     ev, n_ev, params, total, lnl);
+  // 8 proposals per workgroup while 32 would leave CUs without one
+  if (total <= 16384)
+    hipLaunchKernelGGL(k_ragged_epilogue<8>, dim3((unsigned)((total + 7) / 8)), dim3(kThreads), 0, s, ev, n_ev, params,
+                       total, lnl);
+  else
+    hipLaunchKernelGGL(k_ragged_epilogue<32>, dim3((unsigned)((total + 31) / 32)), dim3(kThreads), 0, s, ev, n_ev,
+                       params, total, lnl);
   RBFL_HIP(hipGetLastError());
+}
+
+// Proposals per workgroup of the epilogue.  A batch that leaves the chip short
+// of workgroups waits for one wave's chain of proposals: 4 per workgroup (one
+// per wave, every coefficient load of a lane in flight at once) up to
+// kEpiSmall proposals: 10.1-17.3 us against 14.2-32.9 us with 16 at 1021
+// proposals, 34.4 against 37.5 us at 4096.  Above, 16 keep four workgroups per
+// CU (1.82 ms per 5e5 proposals of 15 pairs against 2.54 ms with 4 and 1.85 ms
+// with 32); with few pairs the setups are a larger share and 32 fill their
+// waves better once there are enough workgroups (0.315 ms against 0.377 ms per
+// 5e5 proposals of one pair, but 25.4 against 20.6 us at 16384).
+constexpr int64_t kEpiSmall = 4096, kEpiLarge = 32768;
+
+template <int EB, int U>
+static void launch_epilogue_variant(const EvalConsts *c, const double *params, int64_t ld, int64_t b0, int64_t nb,
+                                    const double *Y, const double2 *basis, double *lnl, hipStream_t s) {
+  hipLaunchKernelGGL((k_epilogue<EB, U>), dim3((unsigned)((nb + EB - 1) / EB)), dim3(kThreads), 0, s, c, params, ld,
+                     b0, nb, Y, basis, lnl);
 }
 
 void launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
@@ -810,8 +853,12 @@ void launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *pa
     hipLaunchKernelGGL(k_epilogue_banded, dim3((unsigned)((nb + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, c,
                        params, ld, b0, nb, Y, basis, lnl);
   } else {
-    dim3 grid((unsigned)((nb + kEpiBatch - 1) / kEpiBatch));
-    hipLaunchKernelGGL(k_epilogue, grid, dim3(kThreads), 0, s, c, params, ld, b0, nb, Y, basis, lnl);
+    if (nb <= kEpiSmall)
+      launch_epilogue_variant<4, 5>(c, params, ld, b0, nb, Y, basis, lnl, s);
+    else if (nb > kEpiLarge && hc.n_det * hc.n_modes <= 4)
+      launch_epilogue_variant<32, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s);
+    else
+      launch_epilogue_variant<16, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s);
   }
   RBFL_HIP(hipGetLastError());
 }
