@@ -55,6 +55,27 @@ __global__ void __launch_bounds__(256) k_rows_fp64(const EvalConsts *__restrict_
   }
 }
 
+// The same rows for small batches, one row value per thread (t = r ldb + q):
+// k_rows_fp64's 16 exponentials in a row per thread are a chain that a launch
+// of few workgroups waits for.
+__global__ void __launch_bounds__(256) k_rows_small_fp64(const EvalConsts *__restrict__ cp,
+                                                         const double *__restrict__ params, int64_t ld, int64_t b0,
+                                                         int nb, int ldb, int n_rows,
+                                                         const double *__restrict__ nodes, double *__restrict__ Bt) {
+  const EvalConsts &c = *cp;
+  const unsigned t = blockIdx.x * 256 + threadIdx.x;
+  const unsigned r = t / (unsigned)ldb, q = t - r * (unsigned)ldb;
+  if (r >= (unsigned)n_rows) return;
+  double v = 0.0;
+  if ((int)q < nb) {
+    double x[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) x[d] = params[d * ld + b0 + q] / c.semi[d];
+    v = basis_row_fp64((int)r, c.N, c.N + c.M, x, nodes + 4 * (int64_t)r, c.eps2, c.poly_idx);
+  }
+  Bt[(int64_t)r * ldb + q] = v;
+}
+
 // Workgroups are dealt to the 8 XCDs in turn; this gives each XCD a
 // contiguous range of logical tiles (a bijection for any grid size), so the
 // column tiles of one proposal tile run on one XCD and share its L2.
@@ -407,6 +428,136 @@ __global__ void k_zero_item_counter(unsigned long long *counter) {
 // chunks past this bound would only add zeros: the result is the same.
 int gemm_rows(const EvalConsts &hc, int kc) { return (hc.N + hc.M + kc - 1) / kc * kc; }
 
+// Small batches: tiles of WQ x WC waves, 16 RT proposals x 16 CT columns per
+// wave, KC rows per chunk, the loads of the next D chunks in flight in
+// registers, the fragments of the next chunk read ahead.  Bound by the chain of
+// one tile (rows / 4 dependent MFMAs of 64 cycles, 5.4 us for 808 rows) until
+// there are several tiles per SIMD, then by LDS reads and MFMA.  The accumulation runs over the rows in the order of gemm_tile
+// with the same MFMA, so the outputs are the same bit for bit.
+constexpr int kSmallPad = 16;   // doubles per LDS row: two of a fragment's four rows per bank set
+template <int RT, int CT, int KC, int D, int WQ, int WC>
+__global__ void __launch_bounds__(64 * WQ * WC)
+    k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int ldb, int rows, const double *__restrict__ W, int Kp,
+                      double *__restrict__ Y) {
+  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16, NT = 64 * WQ * WC;
+  constexpr int A2 = KC * QT / 2, W2 = KC * CW / 2;
+  constexpr int LA = A2 / NT, LW = W2 / NT;
+  static_assert(KC % 4 == 0 && A2 % NT == 0 && W2 % NT == 0, "whole k-steps, even staging");
+  __shared__ double As[2][KC][QT + kSmallPad];
+  __shared__ double Ws[2][KC][CW + kSmallPad];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wq = wave % WQ, wc = wave / WQ;
+  const int n_ct = Kp / CW;
+  const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int c0 = (int)(tile % n_ct) * CW, q0 = (int)(tile / n_ct) * QT;
+  const double *pa[LA], *pw[LW];
+#pragma unroll
+  for (int u = 0; u < LA; ++u) {
+    const int e = tid + u * NT;
+    // proposals past the padded batch re-read its last pair: their outputs are not stored
+    const int q = q0 + 2 * (e % (QT / 2));
+    pa[u] = Bt + (int64_t)(e / (QT / 2)) * ldb + (q < ldb ? q : ldb - 2);
+  }
+#pragma unroll
+  for (int u = 0; u < LW; ++u) {
+    const int e = tid + u * NT;
+    pw[u] = W + (int64_t)(e / (CW / 2)) * Kp + c0 + 2 * (e % (CW / 2));
+  }
+  const int64_t stepA = (int64_t)KC * ldb, stepW = (int64_t)KC * Kp;
+  const int n_chunks = rows / KC;
+  d2 ra[D][LA], rw[D][LW];
+  // every call loads (past the end the last chunk again), so that the wait
+  // for one set leaves the later ones in flight
+  auto fetch = [&](int ch, d2 *a, d2 *w) {
+    const int64_t at = ch < n_chunks ? ch : n_chunks - 1;
+#pragma unroll
+    for (int u = 0; u < LA; ++u) a[u] = *reinterpret_cast<const d2 *>(pa[u] + at * stepA);
+#pragma unroll
+    for (int u = 0; u < LW; ++u) w[u] = *reinterpret_cast<const d2 *>(pw[u] + at * stepW);
+  };
+  auto stash = [&](int buf, const d2 *a, const d2 *w) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < LA; ++u) {
+      const int e = tid + u * NT;
+      *reinterpret_cast<d2 *>(&As[buf][e / (QT / 2)][2 * (e % (QT / 2))]) = a[u];
+    }
+#pragma unroll
+    for (int u = 0; u < LW; ++u) {
+      const int e = tid + u * NT;
+      *reinterpret_cast<d2 *>(&Ws[buf][e / (CW / 2)][2 * (e % (CW / 2))]) = w[u];
+    }
+  };
+  d4 acc[RT][CT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int u = 0; u < CT; ++u) acc[t][u] = d4{0.0, 0.0, 0.0, 0.0};
+  const int kk = lane >> 4, ll = lane & 15;
+  constexpr int KS = KC / 4;
+  double fa[2][KS][RT], fb[2][KS][CT];     // operand fragments of two chunks
+  auto read = [&](int buf, double (&a)[KS][RT], double (&b)[KS][CT]) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int k = 4 * s + kk;
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[s][t] = As[buf][k][wq * RT * 16 + 16 * t + ll];
+#pragma unroll
+      for (int u = 0; u < CT; ++u) b[s][u] = Ws[buf][k][wc * CT * 16 + 16 * u + ll];
+    }
+  };
+  auto multiply = [&](const double (&a)[KS][RT], const double (&b)[KS][CT]) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int u = 0; u < CT; ++u)
+          acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][t], b[s][u], acc[t][u], 0, 0, 0);
+  };
+  // Step i: the fragments of chunk i + 1 leave LDS, chunk i + 2 goes into the
+  // buffer that held chunk i (its fragments were read before the last
+  // barrier), chunk i + 2 + D starts its way from memory, chunk i is multiplied.
+  // Register set i % D holds chunk i, LDS buffer i % 2 too.
+#pragma unroll
+  for (int i = 0; i < D; ++i) fetch(i, ra[i], rw[i]);
+  stash(0, ra[0], rw[0]);
+  stash(1, ra[1 % D], rw[1 % D]);
+  fetch(D, ra[0], rw[0]);
+  fetch(D + 1, ra[1 % D], rw[1 % D]);
+  __syncthreads();
+  read(0, fa[0], fb[0]);
+  __syncthreads();
+  auto step = [&](int c, int i) {
+    read((i + 1) & 1, fa[(i + 1) & 1], fb[(i + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(i & 1, ra[(i + 2) % D], rw[(i + 2) % D]);
+    fetch(c + 2 + D, ra[(i + 2) % D], rw[(i + 2) % D]);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(fa[i & 1], fb[i & 1]);
+    __syncthreads();
+  };
+  static_assert(D == 2 || D == 4, "even ring");
+  int c = 0;
+  for (; c + D <= n_chunks; c += D) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) step(c + i, i);
+  }
+  if (c < n_chunks) {                      // an even count of chunks: two are left
+    step(c, 0);
+    step(c + 1, 1);
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t q = q0 + wq * RT * 16 + 16 * t + kk + 4 * i;
+      if (q >= nb) continue;
+#pragma unroll
+      for (int u = 0; u < CT; ++u) Y[q * Kp + c0 + wc * CT * 16 + 16 * u + ll] = acc[t][u][i];
+    }
+}
+
 // Basis rows that k_rows_fp64 writes: N + M rounded up to its 16-row groups
 // (at least gemm_rows for chunks of 8 or 16 rows).
 int basis_rows_written(const EvalConsts &hc) { return (hc.N + hc.M + 15) / 16 * 16; }
@@ -422,7 +573,43 @@ void launch_gemm(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc
   RBFL_HIP(hipGetLastError());
 }
 
+template <int RT, int CT, int KC, int D, int WQ, int WC>
+void launch_gemm_small(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc, const double *W, double *Y,
+                       hipStream_t s) {
+  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
+  static_assert(kColTile % CW == 0 && kRowChunk % (2 * KC) == 0, "K is padded to whole tiles, the rows to chunk pairs");
+  const int64_t nblk = (nb + QT - 1) / QT * (hc.Kp / CW);
+  hipLaunchKernelGGL((k_gemm_small_fp64<RT, CT, KC, D, WQ, WC>), dim3((unsigned)nblk), dim3(64 * WQ * WC), 0, s, Bt, (int)nb,
+                     (int)ldb, gemm_rows(hc, 2 * KC), W, hc.Kp, Y);
+  RBFL_HIP(hipGetLastError());
+}
+
 }  // namespace
+
+// Tile of the FP64 contraction for a batch, by its count of 32 x 32 output
+// tiles: 1 = 32 x 32 tiles, 2 = 64 x 64 tiles (k_gemm_small_fp64), 0 = the
+// handle's variant.  The large tiles need several workgroups per CU; below
+// that they wait for one workgroup's chain of chunks (64 x 128 tiles, 808
+// rows: 76-78 us for 1 to 1021 proposals of 1280 columns).  32 x 32 tiles of
+// four waves split such a batch over every SIMD and keep four chunks of loads
+// in flight: 15.5 us for 1, 44.9 us for 1021 proposals (47 TFLOP/s), 43.4
+// against 270.8 us for 1 proposal of 3008 rows and 2560 columns; but a wave
+// with one 16 x 16 tile reads as much LDS as it multiplies (84.5 us at 2048
+// proposals, 602 us on 3008 x 2560).  From 3072 tiles on 64 x 64 tiles (four
+// 16 x 16 tiles per wave) reuse each fragment twice: 161 against 165 and 169 us
+// (variant 0) at 4096 proposals, 301 against 346 us at 8192, 537 against 588 us
+// at 2048 on 3008 x 2560.  From 16384 tiles on the large tiles win (16384
+// proposals: 559 against 590 us).  All give the same bits.
+static int small_tile(const EvalConsts &hc, int64_t nb) {
+  const int64_t tiles = (nb + 31) / 32 * (hc.Kp / 32);
+  return tiles < 3072 ? 1 : tiles < 16384 ? 2 : 0;
+}
+
+// Rows that a batch's contraction reads and k_rows_small_fp64 or k_rows_fp64
+// must write: whole chunk pairs for the small tiles.
+static int rows_needed(const EvalConsts &hc, int64_t nb) {
+  return small_tile(hc, nb) ? hc.rows : basis_rows_written(hc);
+}
 
 int64_t rows_ld(int64_t n) { return (n + 7) & ~int64_t(7); }
 
@@ -461,7 +648,16 @@ double gemm_fp64_reuse(int v) {
 void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                       int64_t nb, const double *nodes, double *Bt, hipStream_t s) {
   const int64_t ldb = rows_ld(nb);
-  dim3 grid((unsigned)((ldb + 255) / 256), (unsigned)(basis_rows_written(hc) / 16));
+  const int n_rows = rows_needed(hc, nb);
+  // one value per thread while that is fewer than four rounds of the chip
+  // (1021 proposals of 832 rows: 9.1 against 10.7 us; 2048: no gain)
+  if (ldb * n_rows <= (1 << 20)) {
+    hipLaunchKernelGGL(k_rows_small_fp64, dim3((unsigned)((ldb * n_rows + 255) / 256)), dim3(256), 0, s, c, params, ld,
+                       b0, (int)nb, (int)ldb, n_rows, nodes, Bt);
+    RBFL_HIP(hipGetLastError());
+    return;
+  }
+  dim3 grid((unsigned)((ldb + 255) / 256), (unsigned)(n_rows / 16));
   hipLaunchKernelGGL(k_rows_fp64, grid, dim3(256), 0, s, c, params, ld, b0, nb, ldb, nodes, Bt);
   RBFL_HIP(hipGetLastError());
 }
@@ -495,6 +691,11 @@ void launch_ragged_gemm_fp64(int variant, const EventDesc *ev, int n_ev, int64_t
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
                       int variant) {
   const int64_t ldb = rows_ld(nb);
+  switch (small_tile(hc, nb)) {
+    case 1: launch_gemm_small<1, 1, 16, 4, 2, 2>(Bt, nb, ldb, hc, W, Y, s); return;
+    case 2: launch_gemm_small<2, 2, 16, 2, 2, 2>(Bt, nb, ldb, hc, W, Y, s); return;
+    default: break;
+  }
   switch (variant) {
     case 0: launch_gemm<2, 4, 8>(Bt, nb, ldb, hc, W, Y, s); break;
     case 1: launch_gemm<4, 2, 8>(Bt, nb, ldb, hc, W, Y, s); break;

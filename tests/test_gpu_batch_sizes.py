@@ -1,0 +1,69 @@
+"""Batch sizes at which the online stage changes kernels: every batch gives
+each proposal the interpolated outputs and ln L of a large batch."""
+import numpy as np
+import pytest
+
+from paper_2508_04172_amd import rbfl
+from paper_2508_04172_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+N_ALL = 70_000
+
+
+@pytest.fixture(scope="module")
+def case():
+    """A handle of 256 padded columns, N_ALL proposals, and their outputs and ln L
+    from large batches (the 64 x 128 tile, 16 proposals per epilogue workgroup)."""
+    import torch
+    cfg = wl.SMALL_MULTI.with_(name="batch_sizes", n_nodes=60, q=12)
+    h = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    idx, jit = wl.node_jitter(N_ALL, cfg.n_nodes)
+    qd = wl.queries(cfg, n=N_ALL).near_nodes(h.nodes(), idx, jit)
+    p = torch.from_numpy(rbfl.params_soa(h, qd, cfg.t_trig)).cuda()
+    h.reserve(N_ALL)
+    return h, p, interp(h, p), lnl(h, p)
+
+
+def interp(h, p):
+    import torch
+    out = torch.empty(p.shape[1], h.sizes()["K"], device="cuda", dtype=torch.float64)
+    h.interp(p.data_ptr(), p.shape[1], out.data_ptr(), rbfl.FORM_FP64, torch.cuda.current_stream().cuda_stream)
+    return out
+
+
+def lnl(h, p):
+    import torch
+    out = torch.empty(p.shape[1], device="cuda", dtype=torch.float64)
+    h.eval(p.data_ptr(), p.shape[1], out.data_ptr(), rbfl.FORM_FP64, torch.cuda.current_stream().cuda_stream)
+    return out.cpu().numpy()
+
+
+# 256 columns are 8 tiles of 32: the tiles change at 3072 / 8 and 16384 / 8 rows
+# of 32 proposals, the epilogue at 4096 proposals; remainders of 16, 32 and 64
+@pytest.mark.parametrize("n", [1, 2, 15, 17, 33, 63, 65, 1021, 4096, 4097, 12255, 12257, 12289, 65503, 65505, 65537])
+def test_batch_size(case, n):
+    import torch
+    h, p, ref, ref_lnl = case
+    cols = slice(N_ALL - n, N_ALL)                    # the tail: other tile positions than in the large batch
+    sub = p[:, cols].contiguous()
+    # the same MFMA over the same rows in the same order: the outputs agree bit for bit
+    assert torch.equal(interp(h, sub), ref[cols])
+    got, want = lnl(h, sub), ref_lnl[cols]
+    fin = np.isfinite(want)
+    assert np.array_equal(fin, np.isfinite(got)) and np.array_equal(np.isnan(want), np.isnan(got))
+    # the epilogue sums fewer than 300 products per proposal, each below 1e5 here
+    # (SNR 20, distances from half the injection's): 300 eps 1e5 < 1e-8
+    assert fin.sum() == 0 or np.abs(got[fin] - want[fin]).max() <= 1e-8
+
+
+@pytest.mark.parametrize("v", range(7))
+def test_large_tiles_agree(case, v):
+    """Each large tile at a batch past the small tiles' range."""
+    import torch
+    h, p, ref, _ = case
+    h.set_variant(rbfl.FORM_FP64, v)
+    try:
+        assert torch.equal(interp(h, p), ref)
+    finally:
+        h.set_variant(rbfl.FORM_FP64, 0)
