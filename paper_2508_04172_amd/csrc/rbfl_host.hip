@@ -1766,10 +1766,8 @@ int32_t rbfl_mlp_loss_grad(rbfl_mlp m, const float *x, const float *t, int64_t B
     rbfl::require(m != nullptr && x != nullptr && t != nullptr && B >= 1 && B <= 65536, "arguments");
     const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     m->m.loss_grad(x, t, B, s);
-    double l = 0.0;
-    RBFL_HIP(hipMemcpyAsync(&l, m->m.loss.p, sizeof(double), hipMemcpyDeviceToHost, s));
     RBFL_HIP(hipStreamSynchronize(s));
-    if (loss) *loss = l;
+    if (loss) *loss = *m->m.loss;
   });
 }
 

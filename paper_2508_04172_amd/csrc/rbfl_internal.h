@@ -147,11 +147,22 @@ struct Mlp {
   int64_t np = 0, o_w1 = 0, o_b1 = 0, o_w2 = 0, o_b2 = 0, o_w3 = 0, o_b3 = 0;
   DevBuf<float> p, g, m, v;
   DevBuf<float> Z1, H1, Z2, H2, Yb, dY, dA, dB;
-  DevBuf<double> part, loss;
-  int64_t cap = 0;
+  DevBuf<double> part;
+  double *loss = nullptr;      // pinned host memory the loss kernel writes; read after its stream
+  DevBuf<float> part1;         // partial gradients of the first layer (few inputs)
+  int64_t cap = 0, grad_cap = 0;
   int t = 0;
+  Mlp() = default;
+  Mlp(const Mlp &) = delete;
+  Mlp &operator=(const Mlp &) = delete;
+  ~Mlp() {
+    if (!loss) return;
+    (void)hipDeviceSynchronize();   // a failed call may have left the loss kernel under way
+    (void)hipHostFree(loss);
+  }
   void init(int n_in, int hidden, int n_out, const double *normals);
   void reserve(int64_t B);
+  void reserve_grad(int64_t B);
   void forward(const float *X, int64_t B, float *Y, hipStream_t s);
   // inference into the interpolant's output layout: Y[b][c] = mu[c] + sd[c] y[b][c]
   // in FP64 (row stride ldy) for c < out, y as forward() computes it; no

@@ -171,9 +171,8 @@ void surrogate_train(Ctx &c, const rbfl_train_spec *sp, hipStream_t s) {
       c.sur->loss_grad(X.p + b0 * 4, T.p + b0 * c.K, sp->batch, s);
       c.sur->adam(sp->lr, sp->beta1, sp->beta2, sp->adam_eps, s);
     }
-    double l = 0.0;
-    RBFL_HIP(hipMemcpyAsync(&l, c.sur->loss.p, sizeof(double), hipMemcpyDeviceToHost, s));
     RBFL_HIP(hipStreamSynchronize(s));
+    const double l = *c.sur->loss;
     if (ep == 0) first = l;
     last = l;
   }

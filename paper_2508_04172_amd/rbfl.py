@@ -659,7 +659,7 @@ class Mlp:
         _check(load().rbfl_mlp_adam(self._p, lr, beta1, beta2, eps, C.c_void_p(stream)))
 
     def get(self, what: int) -> np.ndarray:
-        out = np.zeros(self.n_params, dtype=np.float32)
+        out = np.empty(self.n_params, dtype=np.float32)
         _check(load().rbfl_mlp_get(self._p, what, out.ctypes.data_as(C.c_void_p), out.nbytes))
         return out
 
