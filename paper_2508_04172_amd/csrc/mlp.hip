@@ -689,8 +689,9 @@ void Mlp::infer(const float *X, int64_t B, const float *mu, const float *sd, dou
 // own epilogues: the loss and dY in the output layer's, silu' in the input
 // gradients', the bias gradients in the weight gradients', the first layer's
 // gradients as partial sums of the tiles of dZ1 (never stored); and each
-// stage's two products share a launch.  8 launches, 1024 samples of
-// 4 - 256 - 256 - 1275: 1.65 ms of kernels before.
+// stage's two products share a launch: 1024 samples of 4 - 256 - 256 - 1275 take
+// 86 us in 8 launches, 1.69 ms in 17 with separate elementwise kernels, 64 x 64
+// tiles on 16 to 80 workgroups and one thread per column sum.
 void Mlp::loss_grad(const float *X, const float *T, int64_t B, hipStream_t s) {
   reserve_grad(B);
   const int b = (int)B;

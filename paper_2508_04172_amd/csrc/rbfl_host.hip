@@ -1622,7 +1622,7 @@ int32_t rbfl_brute(rbfl_handle h, const double *params, int64_t n, double *lnl, 
     rbfl::require(params != nullptr && lnl != nullptr, "params/lnl is NULL");
     rbfl::require(n >= 0 && n <= 2147483647, "n must be in 0 .. 2^31 - 1");
     rbfl::Ctx &c = h->c;
-    rbfl::launch_brute(c.consts.p, params, n, n, c.brute_D.p, c.brute_w.p, c.brute_j_lo, c.brute_J, c.n_s, c.df,
+    rbfl::launch_brute(c.consts.p, c.host_consts, params, n, n, c.brute_D.p, c.brute_w.p, c.brute_j_lo, c.brute_J, c.n_s, c.df,
                        1.0 / (c.d_ref * rbfl::kMpcS), lnl, reinterpret_cast<hipStream_t>(stream));
   });
 }

@@ -319,9 +319,9 @@ int window_dft_splits(int nb, int T, int64_t len);
 void launch_window_dft(const double2 *A_mode, int nb, int J_mode, int J_stride, const double2 *Dk, int64_t j_lo,
                        int64_t n_s, int T, int n_split, double2 *partial, hipStream_t s);
 void launch_reduce_splits(const double2 *partial, int n_split, int nb, int T, double2 *Z_rows, hipStream_t s);
-void launch_brute(const EvalConsts *c, const double *params, int64_t ld, int64_t n, const double2 *Dd,
-                  const double *wk, int64_t j_lo, int64_t J, int64_t n_s, double df, double inv_dref_s, double *lnl,
-                  hipStream_t s);
+void launch_brute(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t n,
+                  const double2 *Dd, const double *wk, int64_t j_lo, int64_t J, int64_t n_s, double df,
+                  double inv_dref_s, double *lnl, hipStream_t s);
 void launch_proposal_bins(const EvalConsts *c, const double *params, int64_t ld, int64_t b0, int nb, Binary *bins,
                           hipStream_t s);
 void launch_rotate_band(const double2 *D, int n_det, int64_t J, int64_t j_lo, int64_t n0, int64_t n_s,
