@@ -459,11 +459,13 @@ int32_t rbfl_profile(rbfl_handle h, int32_t on);
  * proposals in columns [sum_{e'<e} counts[e'], ...)) and lnl (FP64 [total]).
  * Execution: one launch writes the FP64 basis rows of every event; a
  * persistent FP64 GEMM kernel then takes (event, proposal tile, column tile)
- * items, events ordered by decreasing cost proposals x (N+M) x K, from an
+ * items, events ordered by decreasing row count N + M, from an
  * atomic counter (reset by a kernel); then the epilogue finishes ln L of each
  * proposal with its own event's frame and basis.  Variants 0-2 instead form
  * the rows inside the persistent contraction (fused), variants 3-4 are the
- * rows + GEMM tiles (the default).  RBFL_PLAN_AUTOTUNE times each variant on
+ * rows + GEMM tiles (the default; a batch of fewer than 8192 output tiles of
+ * 32 x 32 runs smaller tiles, one workgroup per item, in their place, with the
+ * same results).  RBFL_PLAN_AUTOTUNE times each variant on
  * the whole batch (HIP events) and keeps the fastest; RBFL_PLAN_GRAPH captures
  * the launch in a HIP graph, replayed by rbfl_plan_launch -- a sampler step
  * writes new proposals into `params` and launches again, without

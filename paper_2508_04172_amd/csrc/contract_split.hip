@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(256) k_ragged_split_rows(const EventDesc *__re
 
 // Multi-event batches: persistent split contraction over a work list of
 // (event, proposal tile, column tile) items, every event of the list with S
-// digits, column tile fastest within an event, events in decreasing cost;
+// digits, column tile fastest within an event, events in decreasing row count;
 // each workgroup takes the next item from an atomic counter until the list
 // is exhausted (every workgroup reaches that exit).
 template <int S>

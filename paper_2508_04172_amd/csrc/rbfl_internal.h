@@ -106,12 +106,16 @@ struct EventDesc {
 
 // The event of work item `item` in a work list (events in work order, each
 // with the first item of its consecutive range): the last event whose first
-// item is <= item.  The persistent kernels and the host's bounds check
+// item is <= item, by binary search.  The kernels and the host's bounds check
 // (RBFL_DEBUG) share it.
 __host__ __device__ inline int work_event(const EventDesc *ev, int n_ev, int64_t item) {
-  int e = 0;
-  while (e + 1 < n_ev && ev[e + 1].item0 <= item) ++e;
-  return e;
+  int lo = 0, hi = n_ev - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (ev[mid].item0 <= item) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
 }
 
 template <class T>
@@ -372,6 +376,10 @@ void launch_ragged_rows_fp64(const EventDesc *ev, int n_ev, int64_t total_groups
                              const double *params, int64_t ld, hipStream_t s);
 void launch_ragged_gemm_fp64(int variant, const EventDesc *ev, int n_ev, int64_t total_items,
                              unsigned long long *counter, int grid, hipStream_t s);
+// Small-batch tile of a multi-event batch by its count of 32 x 32 output tiles
+// (0: the variant's own), and the contraction with it, one workgroup per item.
+int ragged_small_tile(int64_t tiles);
+void launch_ragged_gemm_small_fp64(int small, const EventDesc *ev, int n_ev, int64_t total_items, hipStream_t s);
 void ragged_tile(int variant, int *proposals_per_tile, int *columns_per_tile);
 void launch_ragged_contract(int variant, const EventDesc *ev, int n_ev, int64_t total_items,
                             unsigned long long *counter, const double *params, int64_t ld, int grid, hipStream_t s);

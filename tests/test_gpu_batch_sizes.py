@@ -67,3 +67,34 @@ def test_large_tiles_agree(case, v):
         assert torch.equal(interp(h, p), ref)
     finally:
         h.set_variant(rbfl.FORM_FP64, 0)
+
+
+# two events of 256 and 128 padded columns: 8 and 4 tiles of 32 per 32 proposals,
+# so the plan's tiles change at 3072 and 16384 of them
+@pytest.mark.parametrize("counts", [(1, 1), (33, 700), (8193, 1), (8000, 8191), (44_000, 9000), (44_001, 43_000)])
+def test_plan_sizes(case, counts):
+    """A two-event plan at sizes on both sides of its tile changes, every rows +
+    GEMM variant pinned, against the per-event evaluation."""
+    import torch
+    h, p, _, _ = case
+    cfg = wl.CFG1.with_(name="plan_sizes", seg_len=8.0, n_nodes=45, q=9)
+    h2 = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    idx, jit = wl.node_jitter(counts[1], cfg.n_nodes)
+    qd = wl.queries(cfg, n=counts[1]).near_nodes(h2.nodes(), idx, jit)
+    p2 = torch.from_numpy(rbfl.params_soa(h2, qd, cfg.t_trig)).cuda()
+    p1 = p[:, :counts[0]].contiguous()
+    want = np.concatenate([lnl(h, p1), lnl(h2, p2)])
+    both = torch.cat([p1, p2], dim=1).contiguous()
+    out = torch.empty(sum(counts), device="cuda", dtype=torch.float64)
+    st = torch.cuda.current_stream().cuda_stream
+    plan = rbfl.Plan([h, h2], counts, both.data_ptr(), out.data_ptr(), rbfl.PLAN_GRAPH, st)
+    for v in (3, 4, 5):
+        plan.set_variant(v, st)
+        for replay in range(2):
+            out.fill_(7.0)
+            plan.launch(st)
+            got = out.cpu().numpy()
+            fin = np.isfinite(want)
+            assert np.array_equal(fin, np.isfinite(got)), f"variant {v}"
+            # the bound of the other multi-event tests: the same products, summed by another kernel
+            assert np.abs(got[fin] - want[fin]).max(initial=0.0) <= 1e-12 * max(1.0, np.abs(want[fin]).max(initial=0.0))
