@@ -379,26 +379,37 @@ __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restr
     epi_reduce<U>(c, su[j], Y + (first + j) * c.Kp, basis4, lnl + b0 + first + j, coef_off, sig_off);
 }
 
-// Epilogue of the time-banded form (n_bands = B > 1): one wave per proposal,
-// one lane per (block v, mode a) pair at a time.  Block v = k B + b is
-// detector k over band b, where mode a sees the source at right ascension
-// alpha - rate (t_c + t_ba - t_trig); that gives the lane its own antenna
-// factor A_va and arrival-time stencil.  The lane reconstructs z_va from all
-// q coefficients (spline-folded basis, as the frozen epilogue) and forms
-// r Re(conj(A_va) z_va) - r^2/2 [|A_va|^2 sigma_aa + 2 sum_{c > a}
-// Re(conj(A_va) A_vc sigma_ac)], taking A_vc from the lanes of the same block
-// (a chunk of lanes holds whole blocks, floor(64 / n_modes) of them).  A
-// stencil outside the window makes the proposal -inf, as in the frozen form;
-// the lanes' terms meet in lane order with compensated additions.
+// Adds v to the compensated (Neumaier) sum (s, c).
+__device__ __forceinline__ void comp_add(double &s, double &c, double v) {
+  const double t = s + v;
+  c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
+  s = t;
+}
+
+// Epilogue of the time-banded form (n_bands = B > 1): one wave per proposal.
+// Block v = k B + b is detector k over band b, where mode a sees the source at
+// right ascension alpha - rate (t_c + t_ba - t_trig); every (block v, mode a)
+// pair so has its own antenna factor A_va and arrival-time stencil.  First a
+// lane per pair forms these, into LDS; then four lanes per pair reconstruct
+// z_va (spline-folded basis, as the frozen epilogue: a pair's lanes read
+// adjacent 64-byte groups, where a lane per pair walked its q entries alone
+// with 64 rows of the basis in every load) and its first lane adds
+// r Re(conj(A_va) z_va); then the lanes stride over the blocks' overlap terms,
+// -r^2/2 |A_va|^2 sigma_aa and -r^2 Re(conj(A_va) A_vc sigma_ac) for c > a.  A
+// stencil outside the window makes the proposal -inf, as in the frozen form.
+// Each lane's sum is compensated, and so is their tree.
+constexpr int kMaxPairs = RBFL_MAX_BLOCKS * RBFL_MAX_MODES;
 __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *__restrict__ cp,
                                                               const double *__restrict__ params, int64_t ld,
                                                               int64_t b0, int64_t nb, const double *__restrict__ Y,
                                                               const double2 *__restrict__ basis4,
                                                               double *__restrict__ lnl) {
+  __shared__ double Ar[kWaves][kMaxPairs], Ai[kWaves][kMaxPairs], F[kWaves][kMaxPairs];
+  __shared__ int N0[kWaves][kMaxPairs];
   const EvalConsts &c = *cp;
-  const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-  if (g >= nb) return;   // whole wave leaves together
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t g = (int64_t)blockIdx.x * kWaves + wave;
+  if (g >= nb) return;   // whole wave leaves together (LDS is per wave: no block barriers)
   double p[11];
   const int pre = epi_prelude(c, params, ld, b0 + g, p);
   if (pre != 0) {   // NaN input, or outside the ellipsoid or the physical region
@@ -410,76 +421,99 @@ __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *
   double ch, sh;
   sincos(0.5 * iota, &sh, &ch);
   const int nm = c.n_modes, q = c.q, T = c.T, B = c.n_bands;
-  const int per = (64 / nm) * nm;
   const int n_pairs = c.n_v * nm;
   const double *y = Y + g * c.Kp;
   bool ok = true;
-  double sum = 0.0, comp = 0.0;
-  for (int p0 = 0; p0 < n_pairs; p0 += per) {
-    const int pr = p0 + lane;
-    const bool active = lane < per && pr < n_pairs;
-    const int v = active ? pr / nm : 0;
-    const int a = active ? pr - v * nm : 0;
+  for (int pr = lane; pr < n_pairs; pr += 64) {
+    const int v = pr / nm, a = pr - v * nm;
     const int k = v / B, bd = v - k * B;
-    double ar = 0.0, ai = 0.0, term = 0.0;
+    const double al = alpha - c.earth_rate * (tc + c.band_t[bd][a] - c.t_trig);
+    double fp, fc, dt;
+    detector_response(c.D[k], c.r[k], al, dec, psi, &fp, &fc, &dt);
+    double ynr, yni, ypr, ypi;
+    eval_ylm(c.ylm_neg[a], ch, sh, phi, &ynr, &yni);
+    eval_ylm(c.ylm_pos[a], ch, sh, phi, &ypr, &ypi);
+    const double sg = (c.mode_l[a] & 1) ? -1.0 : 1.0;
+    Ar[wave][pr] = 0.5 * ((fp * ynr - fc * yni) + sg * (fp * ypr - fc * ypi));
+    Ai[wave][pr] = 0.5 * ((fp * yni + fc * ynr) + sg * (-fp * ypi - fc * ypr));
+    const double s = (tc + dt - c.t_trig) * c.fs + (double)c.half_w;
+    const double fl = floor(s);
+    const bool in = fl >= 4.0 && fl <= (double)(T - 6);
+    ok = ok && in;
+    N0[wave][pr] = in ? (int)fl : 4;
+    F[wave][pr] = s - fl;
+  }
+  if (!__all(ok ? 1 : 0)) {
+    if (lane == 0) lnl[b0 + g] = -__builtin_huge_val();
+    return;
+  }
+  double sum = 0.0, comp = 0.0;
+  const int gl = lane & 3;
+  for (int p0 = 0; p0 < n_pairs; p0 += 16) {
+    const int pr = p0 + (lane >> 2);
+    const bool active = pr < n_pairs;
+    double zr = 0.0, zi = 0.0;
     if (active) {
-      const double al = alpha - c.earth_rate * (tc + c.band_t[bd][a] - c.t_trig);
-      double fp, fc, dt;
-      detector_response(c.D[k], c.r[k], al, dec, psi, &fp, &fc, &dt);
-      double ynr, yni, ypr, ypi;
-      eval_ylm(c.ylm_neg[a], ch, sh, phi, &ynr, &yni);
-      eval_ylm(c.ylm_pos[a], ch, sh, phi, &ypr, &ypi);
-      const double sg = (c.mode_l[a] & 1) ? -1.0 : 1.0;
-      ar = 0.5 * ((fp * ynr - fc * yni) + sg * (fp * ypr - fc * ypi));
-      ai = 0.5 * ((fp * yni + fc * ynr) + sg * (-fp * ypi - fc * ypr));
-      const double s = (tc + dt - c.t_trig) * c.fs + (double)c.half_w;
-      const double fl = floor(s);
-      const bool in = fl >= 4.0 && fl <= (double)(T - 6);
-      ok = ok && in;
-      if (in) {
-        const double f = s - fl;
-        const double2 *base = basis4 + ((int64_t)pr * T + (int)fl) * q * 4;   // pair pr = v n_modes + a
-        const double *cf = y + c.coef_off[v][a];
-        double zr = 0.0, zi = 0.0;
-        for (int i = 0; i < q; ++i) {
-          const double cr = cf[2 * i], ci = cf[2 * i + 1];
-          const double2 w0 = base[4 * i], w1 = base[4 * i + 1], w2 = base[4 * i + 2], w3 = base[4 * i + 3];
-          const double br = fma(fma(fma(w3.x, f, w2.x), f, w1.x), f, w0.x);
-          const double bi = fma(fma(fma(w3.y, f, w2.y), f, w1.y), f, w0.y);
-          zr += cr * br - ci * bi;
-          zi += cr * bi + ci * br;
+      const int v = pr / nm, a = pr - v * nm;
+      const double f = F[wave][pr];
+      const double2 *base = basis4 + ((int64_t)pr * T + N0[wave][pr]) * q * 4;   // pair pr = v n_modes + a
+      const double *cf = y + c.coef_off[v][a];
+      constexpr int U = 2;
+      for (int i0 = gl; i0 < q; i0 += 4 * U) {
+        double2 cc[U], w[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          // past the end: a valid entry is loaded and its coefficient zeroed
+          const bool on = i0 + 4 * u < q;
+          const int i = on ? i0 + 4 * u : i0;
+          const double2 cv = *reinterpret_cast<const double2 *>(cf + 2 * i);
+          cc[u].x = on ? cv.x : 0.0;
+          cc[u].y = on ? cv.y : 0.0;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) w[u][j] = base[4 * i + j];
         }
-        term = rr * (ar * zr + ai * zi);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const double br = fma(fma(fma(w[u][3].x, f, w[u][2].x), f, w[u][1].x), f, w[u][0].x);
+          const double bi = fma(fma(fma(w[u][3].y, f, w[u][2].y), f, w[u][1].y), f, w[u][0].y);
+          zr += cc[u].x * br - cc[u].y * bi;
+          zi += cc[u].x * bi + cc[u].y * br;
+        }
       }
     }
-    // the pair's row of the overlap term; the block's lanes are lead .. lead + nm - 1
-    const int lead = lane - a;
-    const int so = c.sig_off[v];
-    double st = active ? (ar * ar + ai * ai) * y[so + a] : 0.0;
-    for (int cc = 1; cc < nm; ++cc) {
-      const double br = __shfl(ar, (lead + cc) & 63, 64), bi = __shfl(ai, (lead + cc) & 63, 64);
-      if (active && cc > a) {
-        const int idx = a * nm - a * (a + 1) / 2 + (cc - a - 1);   // (a, cc) in lexicographic order
-        const double sr = y[so + nm + 2 * idx], si = y[so + nm + 2 * idx + 1];
-        const double pr_ = ar * br + ai * bi, pi_ = ar * bi - ai * br;
-        st += 2.0 * (pr_ * sr - pi_ * si);
-      }
+#pragma unroll
+    for (int o = 1; o < 4; o <<= 1) {
+      zr += __shfl_xor(zr, o, 64);
+      zi += __shfl_xor(zi, o, 64);
     }
-    term -= 0.5 * rr * rr * st;
-    const double t = sum + term;
-    comp += fabs(sum) >= fabs(term) ? (sum - t) + term : (term - t) + sum;
-    sum = t;
+    if (active && gl == 0) comp_add(sum, comp, rr * (Ar[wave][pr] * zr + Ai[wave][pr] * zi));
   }
-  const bool all_ok = __all(ok ? 1 : 0) != 0;
-  const double mine = sum + comp;
-  double tot = 0.0, tc_ = 0.0;
-  for (int j = 0; j < 64; ++j) {
-    const double vj = __shfl(mine, j, 64);
-    const double t = tot + vj;
-    tc_ += fabs(tot) >= fabs(vj) ? (tot - t) + vj : (vj - t) + tot;
-    tot = t;
+  const int n_terms = nm * (nm + 1) / 2;
+  for (int e = lane; e < c.n_v * n_terms; e += 64) {
+    const int v = e / n_terms;
+    int t = e - v * n_terms;
+    const int so = c.sig_off[v], at = v * nm;
+    if (t < nm) {
+      const double ar = Ar[wave][at + t], ai = Ai[wave][at + t];
+      comp_add(sum, comp, -0.5 * rr * rr * ((ar * ar + ai * ai) * y[so + t]));
+    } else {
+      t -= nm;
+      const int idx = so + nm + 2 * t;
+      int a = 0;                                       // (a, cc) in lexicographic order
+      while (t >= nm - 1 - a) t -= nm - 1 - a++;
+      const int cc = a + 1 + t;
+      const double ar = Ar[wave][at + a], ai = Ai[wave][at + a], br = Ar[wave][at + cc], bi = Ai[wave][at + cc];
+      const double pr_ = ar * br + ai * bi, pi_ = ar * bi - ai * br;
+      comp_add(sum, comp, -rr * rr * (pr_ * y[idx] - pi_ * y[idx + 1]));
+    }
   }
-  if (lane == 0) lnl[b0 + g] = all_ok ? tot + tc_ : -__builtin_huge_val();
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double s2 = __shfl_xor(sum, o, 64), c2 = __shfl_xor(comp, o, 64);
+    comp += c2;
+    comp_add(sum, comp, s2);
+  }
+  if (lane == 0) lnl[b0 + g] = sum + comp;
 }
 
 // Epilogue finished inside the contraction (FP64 form, optional): ln L is
