@@ -6,19 +6,22 @@
 
 namespace rbfl {
 
+// Gaussian row at x of a node xn.
+__device__ __forceinline__ double gauss_row_fp64(const double x[4], const double *xn, double eps2) {
+  double d2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const double t = x[d] - xn[d];
+    d2 = fma(t, t, d2);
+  }
+  return exp(-eps2 * d2);
+}
+
 // Value of basis row `row` at x.  xn: the node's coordinates (row < N);
 // poly[p]: the variable indices of monomial p, -1 = unused.
 __device__ __forceinline__ double basis_row_fp64(int row, int N, int NM, const double x[4], const double *xn,
                                                  double eps2, const int (*poly)[3]) {
-  if (row < N) {
-    double d2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      const double t = x[d] - xn[d];
-      d2 = fma(t, t, d2);
-    }
-    return exp(-eps2 * d2);
-  }
+  if (row < N) return gauss_row_fp64(x, xn, eps2);
   if (row < NM) {
     const int p = row - N;
     double v = 1.0;

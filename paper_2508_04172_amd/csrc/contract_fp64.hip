@@ -199,6 +199,118 @@ __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
   gemm_tile<RT, CT, KC, WQ, WC>(Bt, nb, ldb, rows, W, Kp, Y, tile / n_ct, (int)(tile % n_ct));
 }
 
+constexpr int kFormRowsQ = 64;   // proposals per workgroup of k_rows_gemm_fp64
+
+// Contraction that forms its own rows, for handles whose columns fit one tile
+// (Kp = 128): 64 proposals x all columns per workgroup of 2 x 2 waves, each
+// 2 x 4 tiles of 16 x 16, chunks of KC rows.  With one column tile every row
+// value is used by one workgroup only, so writing it to HBM and reading it back
+// buys nothing: each wave forms its share of the next chunk's rows (a lane per
+// proposal, the nodes in scalar registers) straight into LDS before it
+// multiplies the current one.  FP64 MFMA and VALU work of a SIMD add up, so the
+// exponentials cost a third of the MFMA time (2900 cycles per chunk and
+// workgroup against 2048 of MFMA alone); the rows' round trip costs more
+// (1536 rows, 5e5 proposals: 3.68 ms against 1.22 ms of rows and 3.46 ms of
+// product).  With 256 columns and 8 waves it does not (4.25 against 4.10 ms).
+// Same row values, same MFMA order: the outputs are those of k_gemm_fp64 bit
+// for bit.
+template <int KC>
+__global__ void __launch_bounds__(256)
+    k_rows_gemm_fp64(const EvalConsts *__restrict__ cp, const double *__restrict__ params, int64_t ld, int64_t b0,
+                     int64_t nb, const double *__restrict__ nodes, int rows, const double *__restrict__ W,
+                     double *__restrict__ Y) {
+  constexpr int RT = 2, CT = 4, WQ = 2, QT = kFormRowsQ, CW = 128, NT = 256, NW = 4;
+  constexpr int LW = KC * CW / 2 / NT;     // double2 entries of W per thread and chunk
+  constexpr int PR = KC / NW;              // rows of a chunk that a wave forms
+  static_assert(KC * CW / 2 % NT == 0 && KC % NW == 0 && KC % 4 == 0, "even shares");
+  __shared__ double As[2][KC][QT];
+  __shared__ double Ws[2][KC][CW];
+  const EvalConsts &c = *cp;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wq = wave % WQ, wc = wave / WQ, kk = lane >> 4, ll = lane & 15;
+  const int64_t q0 = xcd_logical_block(blockIdx.x, gridDim.x) * QT;
+  const int N = c.N, NM = c.N + c.M;
+  const double eps2 = c.eps2;
+  double x[4];
+  const int64_t qx = q0 + lane < nb ? q0 + lane : nb - 1;     // past the batch: the last proposal again, not stored
+#pragma unroll
+  for (int d = 0; d < 4; ++d) x[d] = params[d * ld + b0 + qx] / c.semi[d];
+  auto form = [&](int ch, int buf) {
+    const int r0 = ch * KC + wave * PR;
+    double v[PR];
+    if (r0 + PR <= N) {
+#pragma unroll
+      for (int k = 0; k < PR; ++k) v[k] = gauss_row_fp64(x, nodes + 4 * (int64_t)(r0 + k), eps2);
+    } else {
+#pragma unroll
+      for (int k = 0; k < PR; ++k)
+        v[k] = basis_row_fp64(r0 + k, N, NM, x, nodes + 4 * (int64_t)(r0 + k), eps2, c.poly_idx);
+    }
+#pragma unroll
+    for (int k = 0; k < PR; ++k) As[buf][wave * PR + k][lane] = v[k];
+  };
+  const double *pw[LW];
+#pragma unroll
+  for (int u = 0; u < LW; ++u) {
+    const int e = tid + u * NT;
+    pw[u] = W + (int64_t)(e / (CW / 2)) * CW + 2 * (e % (CW / 2));
+  }
+  d2 rw[LW];
+  auto fetch = [&](int ch) {
+#pragma unroll
+    for (int u = 0; u < LW; ++u) rw[u] = *reinterpret_cast<const d2 *>(pw[u] + (int64_t)ch * KC * CW);
+  };
+  auto stash = [&](int buf) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < LW; ++u) {
+      const int e = tid + u * NT;
+      *reinterpret_cast<d2 *>(&Ws[buf][e / (CW / 2)][2 * (e % (CW / 2))]) = rw[u];
+    }
+  };
+  d4 acc[RT][CT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int u = 0; u < CT; ++u) acc[t][u] = d4{0.0, 0.0, 0.0, 0.0};
+  const int n_chunks = rows / KC;
+  fetch(0);
+  form(0, 0);
+  stash(0);
+  __syncthreads();
+  for (int ch = 0; ch < n_chunks; ++ch) {
+    const int cur = ch & 1;
+    if (ch + 1 < n_chunks) {
+      fetch(ch + 1);
+      form(ch + 1, cur ^ 1);
+    }
+#pragma unroll
+    for (int s = 0; s < KC / 4; ++s) {
+      const int k = 4 * s + kk;
+      double a[RT], b[CT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[t] = As[cur][k][wq * RT * 16 + 16 * t + ll];
+#pragma unroll
+      for (int u = 0; u < CT; ++u) b[u] = Ws[cur][k][wc * CT * 16 + 16 * u + ll];
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int u = 0; u < CT; ++u) acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], b[u], acc[t][u], 0, 0, 0);
+    }
+    if (ch + 1 < n_chunks) stash(cur ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t q = q0 + wq * RT * 16 + 16 * t + kk + 4 * i;
+      if (q >= nb) continue;
+#pragma unroll
+      for (int u = 0; u < CT; ++u) Y[q * CW + wc * CT * 16 + 16 * u + ll] = acc[t][u][i];
+    }
+}
+
 // The accumulators of one output tile of Y[q][c] = sum_r Bt[r][q] W[r][c]
 // (the K loop of gemm_tile, kept as a copy so that gemm_tile's code is not
 // changed by this kernel):
@@ -672,6 +784,30 @@ double gemm_fp64_reuse(int v) {
   return qt[v] * cw[v] / (qt[v] + cw[v]);
 }
 
+// How many of a batch's first proposals the contraction forms its own rows for
+// (k_rows_gemm_fp64).  None with more than one column tile, and none while
+// there are fewer than two workgroups per CU, where a workgroup alone waits for
+// its exponentials (1536 rows: 188 against 162 us at 16384 proposals, 279
+// against 315 us at 32768), unless there are few rows, where the separate
+// kernels' start-up counts for more (208 rows: 32 against 39 us at 12288).
+// Otherwise all, but for a last partial round of the chip (three workgroups on
+// each of the 256 CUs) of less than a sixth: one workgroup alone on a CU takes
+// half as long as three together, the small tiles take a quarter of that.
+int64_t gemm_own_rows(const EvalConsts &hc, int64_t nb) {
+  constexpr int64_t kRound = 3 * 256 * kFormRowsQ;
+  if (hc.Kp != 128 || nb < (hc.rows <= 512 ? 12288 : 32768)) return 0;
+  const int64_t rest = nb % kRound;
+  return nb > kRound && rest < kRound / 6 ? nb - rest : nb;
+}
+
+void launch_rows_gemm_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                           int64_t nb, const double *nodes, const double *W, double *Y, hipStream_t s) {
+  constexpr int KC = 16;
+  hipLaunchKernelGGL(k_rows_gemm_fp64<KC>, dim3((unsigned)((nb + kFormRowsQ - 1) / kFormRowsQ)), dim3(256), 0, s, c,
+                     params, ld, b0, nb, nodes, gemm_rows(hc, KC), W, Y);
+  RBFL_HIP(hipGetLastError());
+}
+
 void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                       int64_t nb, const double *nodes, double *Bt, hipStream_t s) {
   const int64_t ldb = rows_ld(nb);
@@ -743,6 +879,16 @@ void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const 
     case 6: launch_gemm<2, 4, 8, 4, 2>(Bt, nb, ldb, hc, W, Y, s); break;
     default: throw Error(RBFL_E_INVALID_ARG, "unknown FP64 GEMM variant");
   }
+}
+
+void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                         int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
+                         int variant, hipEvent_t mid) {
+  const int64_t own = gemm_own_rows(hc, nb);
+  if (own < nb) launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s);
+  if (mid) RBFL_HIP(hipEventRecord(mid, s));
+  if (own > 0) launch_rows_gemm_fp64(c, hc, params, ld, b0, own, nodes, W, Y, s);
+  if (own < nb) launch_gemm_fp64(Bt, nb - own, hc, W, Y + own * hc.Kp, s, variant);
 }
 
 }  // namespace rbfl

@@ -85,7 +85,7 @@ static void eval_pipelined(Ctx &c, const double *params, int64_t ld, int64_t n, 
     const int h = i & 1;
     double *Y = c.Y.p + (size_t)h * half * c.Kp;
     double *Bt = c.Bt.p + (size_t)h * c.rows * half;
-    hipEvent_t ev[6];
+    hipEvent_t ev[5];
     auto mark = [&](int k, hipStream_t st) {
       if (c.profile) RBFL_HIP(hipEventRecord(ev[k], st));
     };
@@ -94,24 +94,26 @@ static void eval_pipelined(Ctx &c, const double *params, int64_t ld, int64_t n, 
         RBFL_HIP(hipEventCreate(&e));
         c.timed_events.push_back(e);
       }
-    mark(0, s);
-    if (two_stage) launch_rows_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, Bt, s);
-    mark(1, s);
     if (i >= 2) RBFL_HIP(hipStreamWaitEvent(s, c.pev_epi[h], 0));
+    mark(0, s);
+    if (two_stage) {
+      launch_product_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, Bt, Y, s, v,
+                          c.profile ? ev[1] : nullptr);
+    } else {
+      mark(1, s);
+      launch_contract_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, Y, s, 2);
+    }
     mark(2, s);
-    if (two_stage) launch_gemm_fp64(Bt, nb, c.host_consts, c.W.p, Y, s, v);
-    else launch_contract_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, Y, s, 2);
-    mark(3, s);
     RBFL_HIP(hipEventRecord(c.pev_prod[h], s));
     RBFL_HIP(hipStreamWaitEvent(c.side, c.pev_prod[h], 0));
-    mark(4, c.side);
+    mark(3, c.side);
     launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, Y, c.basis4.p, lnl, c.side);
-    mark(5, c.side);
+    mark(4, c.side);
     RBFL_HIP(hipEventRecord(c.pev_epi[h], c.side));
     if (c.profile) {
       if (two_stage) c.timed.push_back(Ctx::Timed{ev[0], ev[1], 2, nb});
-      c.timed.push_back(Ctx::Timed{ev[2], ev[3], 0, nb});
-      c.timed.push_back(Ctx::Timed{ev[4], ev[5], 1, nb});
+      c.timed.push_back(Ctx::Timed{ev[1], ev[2], 0, nb});
+      c.timed.push_back(Ctx::Timed{ev[3], ev[4], 1, nb});
     }
   }
   for (int h = 0; h < std::min(i, 2); ++h) RBFL_HIP(hipStreamWaitEvent(s, c.pev_epi[h], 0));
@@ -249,9 +251,8 @@ static void contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64
   auto fp64 = [&]() {
     const int v = c.variant[RBFL_FORM_FP64];
     if (v < gemm_fp64_variants()) {
-      launch_rows_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.Bt.p, s);
-      mark(1);
-      launch_gemm_fp64(c.Bt.p, nb, c.host_consts, c.W.p, c.Y.p, s, v);
+      launch_product_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Bt.p, c.Y.p, s, v,
+                          marks ? marks[1] : nullptr);
     } else {
       mark(1);
       launch_contract_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Y.p, s, 2);

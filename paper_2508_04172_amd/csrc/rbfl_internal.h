@@ -355,6 +355,12 @@ int64_t rows_ld(int64_t n);
 int gemm_fp64_variants();
 const char *gemm_fp64_variant_name(int variant);
 double gemm_fp64_reuse(int variant);
+// The FP64 product Y of proposals b0 .. b0 + nb - 1 with tile `variant` (below
+// gemm_fp64_variants()): basis rows into Bt and their contraction, or in one
+// kernel where that is better; mid, when given, is recorded between the two.
+void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                         int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
+                         int variant, hipEvent_t mid);
 void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                       int64_t nb, const double *nodes, double *Bt, hipStream_t s);
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,

@@ -69,8 +69,7 @@ void eval_static(Ctx &c, const double *params, int64_t n, double *lnl, hipStream
   for (int64_t b0 = 0; b0 < n; b0 += chunk) {
     const int64_t nb = std::min(chunk, n - b0);
     if (v < gemm_fp64_variants()) {
-      launch_rows_fp64(c.consts.p, c.host_consts, params, n, b0, nb, c.nodes.p, Bt, s);
-      launch_gemm_fp64(Bt, nb, c.host_consts, c.W.p, Y, s, v);
+      launch_product_fp64(c.consts.p, c.host_consts, params, n, b0, nb, c.nodes.p, c.W.p, Bt, Y, s, v, nullptr);
     } else {
       launch_contract_fp64(c.consts.p, c.host_consts, params, n, b0, nb, c.nodes.p, c.W.p, Y, s, 2);
     }

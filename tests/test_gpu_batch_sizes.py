@@ -98,3 +98,23 @@ def test_plan_sizes(case, counts):
             assert np.array_equal(fin, np.isfinite(got)), f"variant {v}"
             # the bound of the other multi-event tests: the same products, summed by another kernel
             assert np.abs(got[fin] - want[fin]).max(initial=0.0) <= 1e-12 * max(1.0, np.abs(want[fin]).max(initial=0.0))
+
+
+# one column tile (128): the contraction forms its own rows from 12288 proposals on
+# with few rows, from 32768 on with more than 512, except for a last partial round
+# of less than 8192 past each 49152
+@pytest.mark.parametrize("nodes, n", [(45, 12287), (45, 12288), (45, 12351), (45, 49152), (45, 49153), (45, 57343),
+                                      (45, 57345), (500, 12289), (600, 32767), (600, 32769), (600, 49217)])
+def test_one_column_tile(nodes, n):
+    """Batches on both sides of the rule against the same proposals in slices
+    below it: the same row values and MFMA order, so the same bits."""
+    import torch
+    cfg = wl.CFG1.with_(name="one_tile", seg_len=8.0, n_nodes=nodes, q=9, poly_degree=3)
+    h = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    idx, jit = wl.node_jitter(n, cfg.n_nodes)
+    qd = wl.queries(cfg, n=n).near_nodes(h.nodes(), idx, jit)
+    p = torch.from_numpy(rbfl.params_soa(h, qd, cfg.t_trig)).cuda()
+    h.reserve(n)
+    got = interp(h, p)
+    for b in range(0, n, 8192):
+        assert torch.equal(interp(h, p[:, b:b + 8192].contiguous()), got[b:b + 8192])
