@@ -463,7 +463,7 @@ int32_t rbfl_profile(rbfl_handle h, int32_t on);
  * atomic counter (reset by a kernel); then the epilogue finishes ln L of each
  * proposal with its own event's frame and basis.  Variants 0-2 instead form
  * the rows inside the persistent contraction (fused), variants 3-4 are the
- * rows + GEMM tiles (the default; a batch of fewer than 8192 output tiles of
+ * rows + GEMM tiles (the default; a batch of fewer than 22000 output tiles of
  * 32 x 32 runs smaller tiles, one workgroup per item, in their place, with the
  * same results).  RBFL_PLAN_AUTOTUNE times each variant on
  * the whole batch (HIP events) and keeps the fastest; RBFL_PLAN_GRAPH captures

@@ -16,6 +16,8 @@
 // v_mfma_f64_16x16x4f64 (lane l holds A[l%16][l/16], B[l/16][l%16];
 // accumulator element i is D[l/16 + 4i][l%16], measured on gfx950); row
 // chunks of KC rows of both operands staged through LDS, double-buffered.
+#include <algorithm>
+
 #include "basis_rows.h"
 #include "epilogue_setup.h"
 #include "rbfl_internal.h"
@@ -531,6 +533,15 @@ __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
   }
 }
 
+// The 64 x 64 tile over the work list, one workgroup per item: its items are too
+// short to wait for the counter in between.
+__global__ void __launch_bounds__(256, 2) k_ragged_gemm_mid_fp64(const EventDesc *__restrict__ ev, int n_ev) {
+  const int64_t item = blockIdx.x;
+  const EventDesc &d = ev[work_event(ev, n_ev, item)];
+  const int local = (int)(item - d.item0);
+  gemm_tile<2, 2, 8>(d.Bt, d.n, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c, local % d.tiles_c);
+}
+
 __global__ void k_zero_item_counter(unsigned long long *counter) {
   if (threadIdx.x == 0) *counter = 0ull;
 }
@@ -540,113 +551,77 @@ __global__ void k_zero_item_counter(unsigned long long *counter) {
 // chunks past this bound would only add zeros: the result is the same.
 int gemm_rows(const EvalConsts &hc, int kc) { return (hc.N + hc.M + kc - 1) / kc * kc; }
 
-// Small batches: tiles of WQ x WC waves, 16 RT proposals x 16 CT columns per
-// wave, KC rows per chunk, the loads of the next D chunks in flight in
-// registers, the fragments of the next chunk read ahead.  Bound by the chain of
-// one tile (rows / 4 dependent MFMAs of 64 cycles, 5.4 us for 808 rows) until
-// there are several tiles per SIMD, then by LDS reads and MFMA.  The accumulation runs over the rows in the order of gemm_tile
-// with the same MFMA, so the outputs are the same bit for bit.
-constexpr int kSmallPad = 16;   // doubles per LDS row: two of a fragment's four rows per bank set
-template <int RT, int CT, int KC, int D, int WQ, int WC>
-__device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, int nb, int ldb, int rows,
+// Small batches: 32 x 32 tiles of four waves (2 x 2), each one 16 x 16 tile;
+// chunks of kTinyKC rows, the loads of the next four in flight in registers, the
+// fragments of the next chunk read ahead.  Bound by the chain of one tile (rows /
+// 4 dependent MFMAs of 64 cycles, 5.4 us for 808 rows) until there are several
+// tiles per SIMD, then by LDS reads and MFMA.  The accumulation runs over the
+// rows in the order of gemm_tile with the same MFMA, so the outputs are the same
+// bit for bit.
+constexpr int kTinyTile = 32, kTinyKC = 16;
+constexpr int kTinyPad = 16;   // doubles per LDS row: two of a fragment's four rows per bank set
+__device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, int nb, int64_t ldb, int rows,
                                                 const double *__restrict__ W, int Kp, double *__restrict__ Y, int q0,
                                                 int c0) {
-  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16, NT = 64 * WQ * WC;
-  constexpr int A2 = KC * QT / 2, W2 = KC * CW / 2;
-  constexpr int LA = A2 / NT, LW = W2 / NT;
-  static_assert(KC % 4 == 0 && A2 % NT == 0 && W2 % NT == 0, "whole k-steps, even staging");
-  __shared__ double As[2][KC][QT + kSmallPad];
-  __shared__ double Ws[2][KC][CW + kSmallPad];
+  constexpr int T = kTinyTile, KC = kTinyKC, KS = KC / 4, D = 4;
+  static_assert(KC * T / 2 == 256, "one double2 of each operand per thread and chunk");
+  __shared__ double As[2][KC][T + kTinyPad];
+  __shared__ double Ws[2][KC][T + kTinyPad];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wq = wave % WQ, wc = wave / WQ;
-  const double *pa[LA], *pw[LW];
-#pragma unroll
-  for (int u = 0; u < LA; ++u) {
-    const int e = tid + u * NT;
-    // proposals past the padded batch re-read its last pair: their outputs are not stored
-    const int q = q0 + 2 * (e % (QT / 2));
-    pa[u] = Bt + (int64_t)(e / (QT / 2)) * ldb + (q < ldb ? q : ldb - 2);
-  }
-#pragma unroll
-  for (int u = 0; u < LW; ++u) {
-    const int e = tid + u * NT;
-    pw[u] = W + (int64_t)(e / (CW / 2)) * Kp + c0 + 2 * (e % (CW / 2));
-  }
-  const int64_t stepA = (int64_t)KC * ldb, stepW = (int64_t)KC * Kp;
+  const int wq = wave & 1, wc = wave >> 1, kk = lane >> 4, ll = lane & 15;
+  const int sk = tid / (T / 2), sm = 2 * (tid % (T / 2));
+  // proposals past the batch (padded to 8) re-read its last pair: their outputs are not stored
+  const int end = (nb + 7) & ~7;
+  const double *pa = Bt + (int64_t)sk * ldb + (q0 + sm < end ? q0 + sm : end - 2);
+  const double *pw = W + (int64_t)sk * Kp + c0 + sm;
+  const int64_t stepA = KC * ldb, stepW = (int64_t)KC * Kp;
   const int n_chunks = rows / KC;
-  d2 ra[D][LA], rw[D][LW];
+  d2 ra[D], rw[D];
   // every call loads (past the end the last chunk again), so that the wait
   // for one set leaves the later ones in flight
-  auto fetch = [&](int ch, d2 *a, d2 *w) {
+  auto fetch = [&](int ch, int i) {
     const int64_t at = ch < n_chunks ? ch : n_chunks - 1;
-#pragma unroll
-    for (int u = 0; u < LA; ++u) a[u] = *reinterpret_cast<const d2 *>(pa[u] + at * stepA);
-#pragma unroll
-    for (int u = 0; u < LW; ++u) w[u] = *reinterpret_cast<const d2 *>(pw[u] + at * stepW);
+    ra[i] = *reinterpret_cast<const d2 *>(pa + at * stepA);
+    rw[i] = *reinterpret_cast<const d2 *>(pw + at * stepW);
   };
-  auto stash = [&](int buf, const d2 *a, const d2 *w) {
+  auto stash = [&](int buf, int i) {
     asm volatile("" ::: "memory");
-#pragma unroll
-    for (int u = 0; u < LA; ++u) {
-      const int e = tid + u * NT;
-      *reinterpret_cast<d2 *>(&As[buf][e / (QT / 2)][2 * (e % (QT / 2))]) = a[u];
-    }
-#pragma unroll
-    for (int u = 0; u < LW; ++u) {
-      const int e = tid + u * NT;
-      *reinterpret_cast<d2 *>(&Ws[buf][e / (CW / 2)][2 * (e % (CW / 2))]) = w[u];
-    }
+    *reinterpret_cast<d2 *>(&As[buf][sk][sm]) = ra[i];
+    *reinterpret_cast<d2 *>(&Ws[buf][sk][sm]) = rw[i];
   };
-  d4 acc[RT][CT];
-#pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int u = 0; u < CT; ++u) acc[t][u] = d4{0.0, 0.0, 0.0, 0.0};
-  const int kk = lane >> 4, ll = lane & 15;
-  constexpr int KS = KC / 4;
-  double fa[2][KS][RT], fb[2][KS][CT];     // operand fragments of two chunks
-  auto read = [&](int buf, double (&a)[KS][RT], double (&b)[KS][CT]) {
+  d4 acc = d4{0.0, 0.0, 0.0, 0.0};
+  double fa[2][KS], fb[2][KS];     // operand fragments of two chunks
+  auto read = [&](int buf) {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const int k = 4 * s + kk;
-#pragma unroll
-      for (int t = 0; t < RT; ++t) a[s][t] = As[buf][k][wq * RT * 16 + 16 * t + ll];
-#pragma unroll
-      for (int u = 0; u < CT; ++u) b[s][u] = Ws[buf][k][wc * CT * 16 + 16 * u + ll];
+      fa[buf][s] = As[buf][4 * s + kk][wq * 16 + ll];
+      fb[buf][s] = Ws[buf][4 * s + kk][wc * 16 + ll];
     }
-  };
-  auto multiply = [&](const double (&a)[KS][RT], const double (&b)[KS][CT]) {
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int u = 0; u < CT; ++u)
-          acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][t], b[s][u], acc[t][u], 0, 0, 0);
   };
   // Step i: the fragments of chunk i + 1 leave LDS, chunk i + 2 goes into the
   // buffer that held chunk i (its fragments were read before the last
   // barrier), chunk i + 2 + D starts its way from memory, chunk i is multiplied.
-  // Register set i % D holds chunk i, LDS buffer i % 2 too.
+  // Register set i % D and LDS buffer i % 2 hold chunk i.
 #pragma unroll
-  for (int i = 0; i < D; ++i) fetch(i, ra[i], rw[i]);
-  stash(0, ra[0], rw[0]);
-  stash(1, ra[1 % D], rw[1 % D]);
-  fetch(D, ra[0], rw[0]);
-  fetch(D + 1, ra[1 % D], rw[1 % D]);
+  for (int i = 0; i < D; ++i) fetch(i, i);
+  stash(0, 0);
+  stash(1, 1);
+  fetch(D, 0);
+  fetch(D + 1, 1);
   __syncthreads();
-  read(0, fa[0], fb[0]);
+  read(0);
   __syncthreads();
   auto step = [&](int c, int i) {
-    read((i + 1) & 1, fa[(i + 1) & 1], fb[(i + 1) & 1]);
+    read((i + 1) & 1);
     __builtin_amdgcn_sched_barrier(0);
-    stash(i & 1, ra[(i + 2) % D], rw[(i + 2) % D]);
-    fetch(c + 2 + D, ra[(i + 2) % D], rw[(i + 2) % D]);
+    stash(i & 1, (i + 2) % D);
+    fetch(c + 2 + D, (i + 2) % D);
     __builtin_amdgcn_sched_barrier(0);
-    multiply(fa[i & 1], fb[i & 1]);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i & 1][s], fb[i & 1][s], acc, 0, 0, 0);
     __syncthreads();
   };
-  static_assert(D == 2 || D == 4, "even ring");
   int c = 0;
   for (; c + D <= n_chunks; c += D) {
 #pragma unroll
@@ -657,39 +632,30 @@ __device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, i
     step(c + 1, 1);
   }
 #pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t q = q0 + wq * RT * 16 + 16 * t + kk + 4 * i;
-      if (q >= nb) continue;
-#pragma unroll
-      for (int u = 0; u < CT; ++u) Y[q * Kp + c0 + wc * CT * 16 + 16 * u + ll] = acc[t][u][i];
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int64_t q = q0 + wq * 16 + kk + 4 * i;
+    if (q < nb) Y[q * Kp + c0 + wc * 16 + ll] = acc[i];
+  }
 }
 
-template <int RT, int CT, int KC, int D, int WQ, int WC>
-__global__ void __launch_bounds__(64 * WQ * WC)
-    k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int ldb, int rows, const double *__restrict__ W, int Kp,
-                      double *__restrict__ Y) {
-  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
-  const int n_ct = Kp / CW;
+__global__ void __launch_bounds__(256)
+    k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int64_t ldb, int rows, const double *__restrict__ W,
+                      int Kp, double *__restrict__ Y) {
+  const int n_ct = Kp / kTinyTile;
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
-  gemm_small_tile<RT, CT, KC, D, WQ, WC>(Bt, nb, ldb, rows, W, Kp, Y, (int)(tile / n_ct) * QT, (int)(tile % n_ct) * CW);
+  gemm_small_tile(Bt, nb, ldb, rows, W, Kp, Y, (int)(tile / n_ct) * kTinyTile, (int)(tile % n_ct) * kTinyTile);
 }
 
 // The small tiles over the work list of a multi-event batch, one workgroup per
 // item (events in decreasing row count, so the longest items start first).
-template <int RT, int CT, int KC, int D, int WQ, int WC>
-__global__ void __launch_bounds__(64 * WQ * WC)
-    k_ragged_gemm_small_fp64(const EventDesc *__restrict__ ev, int n_ev) {
-  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
+__global__ void __launch_bounds__(256) k_ragged_gemm_small_fp64(const EventDesc *__restrict__ ev, int n_ev) {
   const int64_t item = blockIdx.x;
   const EventDesc &d = ev[work_event(ev, n_ev, item)];
   const int local = (int)(item - d.item0);
   const EvalConsts &c = *d.consts;
-  const int rows = (c.N + c.M + 2 * KC - 1) / (2 * KC) * (2 * KC);
-  gemm_small_tile<RT, CT, KC, D, WQ, WC>(d.Bt, (int)d.n, (int)d.ldb, rows, d.W, d.Kp, d.Y, local / d.tiles_c * QT,
-                                         local % d.tiles_c * CW);
+  const int rows = (c.N + c.M + 2 * kTinyKC - 1) / (2 * kTinyKC) * (2 * kTinyKC);
+  gemm_small_tile(d.Bt, (int)d.n, d.ldb, rows, d.W, d.Kp, d.Y, local / d.tiles_c * kTinyTile,
+                  local % d.tiles_c * kTinyTile);
 }
 
 // Basis rows that k_rows_fp64 writes: N + M rounded up to its 16-row groups
@@ -707,48 +673,60 @@ void launch_gemm(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc
   RBFL_HIP(hipGetLastError());
 }
 
-template <int RT, int CT, int KC, int D, int WQ, int WC>
 void launch_gemm_small(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc, const double *W, double *Y,
                        hipStream_t s) {
-  constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
-  static_assert(kColTile % CW == 0 && kRowChunk % (2 * KC) == 0, "K is padded to whole tiles, the rows to chunk pairs");
-  const int64_t nblk = (nb + QT - 1) / QT * (hc.Kp / CW);
-  hipLaunchKernelGGL((k_gemm_small_fp64<RT, CT, KC, D, WQ, WC>), dim3((unsigned)nblk), dim3(64 * WQ * WC), 0, s, Bt, (int)nb,
-                     (int)ldb, gemm_rows(hc, 2 * KC), W, hc.Kp, Y);
+  static_assert(kColTile % kTinyTile == 0 && kRowChunk % (2 * kTinyKC) == 0, "whole tiles and chunk pairs");
+  const int64_t nblk = (nb + kTinyTile - 1) / kTinyTile * (hc.Kp / kTinyTile);
+  hipLaunchKernelGGL(k_gemm_small_fp64, dim3((unsigned)nblk), dim3(256), 0, s, Bt, (int)nb, ldb,
+                     gemm_rows(hc, 2 * kTinyKC), W, hc.Kp, Y);
   RBFL_HIP(hipGetLastError());
 }
 
 }  // namespace
 
-// Tile of the FP64 contraction for a batch, by its count of 32 x 32 output
-// tiles: 1 = 32 x 32 tiles, 2 = 64 x 64 tiles (k_gemm_small_fp64), 0 = the
-// handle's variant.  The large tiles need several workgroups per CU; below
-// that they wait for one workgroup's chain of chunks (64 x 128 tiles, 808
-// rows: 76-78 us for 1 to 1021 proposals of 1280 columns).  32 x 32 tiles of
-// four waves split such a batch over every SIMD and keep four chunks of loads
-// in flight: 15.5 us for 1, 44.9 us for 1021 proposals (47 TFLOP/s), 43.4
-// against 270.8 us for 1 proposal of 3008 rows and 2560 columns; but a wave
-// with one 16 x 16 tile reads as much LDS as it multiplies (84.5 us at 2048
-// proposals, 602 us on 3008 x 2560).  From 3072 tiles on 64 x 64 tiles (four
-// 16 x 16 tiles per wave) reuse each fragment twice: 161 against 165 and 169 us
-// (variant 0) at 4096 proposals, 301 against 346 us at 8192, 537 against 588 us
-// at 2048 on 3008 x 2560.  From 16384 tiles on the large tiles win (16384
-// proposals: 559 against 590 us).  All give the same bits.
-static int small_tile(const EvalConsts &hc, int64_t nb) {
-  const int64_t tiles = (nb + 31) / 32 * (hc.Kp / 32);
-  return tiles < 3072 ? 1 : tiles < 16384 ? 2 : 0;
+// Tiles of the FP64 contraction by a batch's count of 32 x 32 output tiles: below
+// kTinyTiles 32 x 32 (k_gemm_small_fp64), below kMidTiles 64 x 64 (variant 4's),
+// from there on the handle's variant.  A large tile waits for one workgroup's
+// chain of chunks while there is less than a round of them (64 x 128, 808 rows:
+// 75-79 us for 512 to 1021 proposals of 1280 columns, 33 and 50 us with 32 x 32
+// tiles), and its last rounds are coarse; a wave with one 16 x 16 tile reads as
+// much LDS as it multiplies.  us for 32 x 32 / 64 x 64 / best large tile, 808
+// rows x 1280 columns: 88 / 95 / 117 at 2048 proposals (2560 tiles), 129 / 118 /
+// 118 at 3000 (3760), 331 / 288 / 316 at 8192, 633 / 519 / 526 at 16384 (20480);
+// 3008 rows x 2560 columns: 299 / 329 / 411 at 1021 (2560), 435 / 408 / 413 at
+// 1500 (3760), 1138 / 982 / 1152 at 4000, 2343 / 1922 / 1921 at 8192 (20480).
+// All give the same bits.
+constexpr int64_t kTinyTiles = 2880, kMidTiles = 22000;
+static int64_t tiles32(const EvalConsts &hc, int64_t nb) { return (nb + 31) / 32 * (hc.Kp / 32); }
+
+// How many of a batch's first proposals the variant's tile takes; the rest goes
+// to the smaller ones.  None below kMidTiles.  The 8-wave tiles (256 x 128, one
+// workgroup per CU; 128 x 128, two) leave half the chip idle in a short last
+// round, so they hand it over where the smaller tiles take less: with two per CU
+// up to 0.4 of a round (which would cost half of one) and from 0.5 to 0.75 (a
+// whole one): 7.30 to 6.84 ms at 30011 proposals of 3008 rows and 2560 columns
+// (9.2 rounds).
+static int64_t main_part(const EvalConsts &hc, int64_t nb, int variant) {
+  if (tiles32(hc, nb) < kMidTiles) return 0;
+  if (variant != 5 && variant != 6) return nb;
+  const int64_t qt = variant == 5 ? 256 : 128, round = variant == 5 ? 256 : 512, n_ct = hc.Kp / 128;
+  const int64_t tiles = (nb + qt - 1) / qt * n_ct, rest = tiles % round;
+  const bool hand_over = 4 * rest < 3 * round && (variant == 5 || 5 * rest < 2 * round || 2 * rest > round);
+  return hand_over ? std::min(nb, (tiles - rest) / n_ct * qt) : nb;
 }
 
-// The same for a multi-event batch, whose tiles differ in length: 64 x 64 tiles
-// win at 4096 tiles (129 against 143 us for 4 events of 1000 proposals), at
-// 11,440 the variant's do (401 against 449 us for 12 events).
-int ragged_small_tile(int64_t tiles) { return tiles < 3072 ? 1 : tiles < 8192 ? 2 : 0; }
-
-// Rows that a batch's contraction reads and k_rows_small_fp64 or k_rows_fp64
-// must write: whole chunk pairs for the small tiles.
-static int rows_needed(const EvalConsts &hc, int64_t nb) {
-  return small_tile(hc, nb) ? hc.rows : basis_rows_written(hc);
+// Rows that a batch's contraction with `variant` (-1: the fused epilogue's) reads
+// and the row kernels must write: whole chunk pairs where 32 x 32 tiles take a part.
+static int rows_needed(const EvalConsts &hc, int64_t nb, int variant) {
+  if (variant < 0) return basis_rows_written(hc);
+  const int64_t rest = nb - main_part(hc, nb, variant);
+  return rest > 0 && tiles32(hc, rest) < kTinyTiles ? hc.rows : basis_rows_written(hc);
 }
+
+// The same for a multi-event batch: 1 = 32 x 32, 2 = 64 x 64 tiles, 0 = the
+// plan's variant (64 x 64 / variant: 129 / 145 us for 4 events of 1000 proposals,
+// 4096 tiles; 385 / 400 us for 12, 11,440 tiles).
+int ragged_small_tile(int64_t tiles) { return tiles < kTinyTiles ? 1 : tiles < kMidTiles ? 2 : 0; }
 
 int64_t rows_ld(int64_t n) { return (n + 7) & ~int64_t(7); }
 
@@ -809,9 +787,9 @@ void launch_rows_gemm_fp64(const EvalConsts *c, const EvalConsts &hc, const doub
 }
 
 void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s) {
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant) {
   const int64_t ldb = rows_ld(nb);
-  const int n_rows = rows_needed(hc, nb);
+  const int n_rows = rows_needed(hc, nb, variant);
   // one value per thread while that is fewer than four rounds of the chip
   // (1021 proposals of 832 rows: 9.1 against 10.7 us; 2048: no gain)
   if (ldb * n_rows <= (1 << 20)) {
@@ -853,39 +831,37 @@ void launch_ragged_gemm_fp64(int variant, const EventDesc *ev, int n_ev, int64_t
 
 void launch_ragged_gemm_small_fp64(int small, const EventDesc *ev, int n_ev, int64_t total_items, hipStream_t s) {
   if (small == 1)
-    hipLaunchKernelGGL((k_ragged_gemm_small_fp64<1, 1, 16, 4, 2, 2>), dim3((unsigned)total_items), dim3(256), 0, s, ev,
-                       n_ev);
+    hipLaunchKernelGGL(k_ragged_gemm_small_fp64, dim3((unsigned)total_items), dim3(256), 0, s, ev, n_ev);
   else
-    hipLaunchKernelGGL((k_ragged_gemm_small_fp64<2, 2, 16, 2, 2, 2>), dim3((unsigned)total_items), dim3(256), 0, s, ev,
-                       n_ev);
+    hipLaunchKernelGGL(k_ragged_gemm_mid_fp64, dim3((unsigned)total_items), dim3(256), 0, s, ev, n_ev);
   RBFL_HIP(hipGetLastError());
 }
 
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
                       int variant) {
-  const int64_t ldb = rows_ld(nb);
-  switch (small_tile(hc, nb)) {
-    case 1: launch_gemm_small<1, 1, 16, 4, 2, 2>(Bt, nb, ldb, hc, W, Y, s); return;
-    case 2: launch_gemm_small<2, 2, 16, 2, 2, 2>(Bt, nb, ldb, hc, W, Y, s); return;
-    default: break;
-  }
-  switch (variant) {
-    case 0: launch_gemm<2, 4, 8>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 1: launch_gemm<4, 2, 8>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 2: launch_gemm<2, 4, 16>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 3: launch_gemm<4, 2, 16>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 4: launch_gemm<2, 2, 8>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 5: launch_gemm<4, 4, 8, 4, 2>(Bt, nb, ldb, hc, W, Y, s); break;
-    case 6: launch_gemm<2, 4, 8, 4, 2>(Bt, nb, ldb, hc, W, Y, s); break;
-    default: throw Error(RBFL_E_INVALID_ARG, "unknown FP64 GEMM variant");
-  }
+  if (variant < 0 || variant >= gemm_fp64_variants()) throw Error(RBFL_E_INVALID_ARG, "unknown FP64 GEMM variant");
+  const int64_t ldb = rows_ld(nb), n1 = main_part(hc, nb, variant), n2 = nb - n1;
+  if (n1 > 0) switch (variant) {
+      case 0: launch_gemm<2, 4, 8>(Bt, n1, ldb, hc, W, Y, s); break;
+      case 1: launch_gemm<4, 2, 8>(Bt, n1, ldb, hc, W, Y, s); break;
+      case 2: launch_gemm<2, 4, 16>(Bt, n1, ldb, hc, W, Y, s); break;
+      case 3: launch_gemm<4, 2, 16>(Bt, n1, ldb, hc, W, Y, s); break;
+      case 4: launch_gemm<2, 2, 8>(Bt, n1, ldb, hc, W, Y, s); break;
+      case 5: launch_gemm<4, 4, 8, 4, 2>(Bt, n1, ldb, hc, W, Y, s); break;
+      default: launch_gemm<2, 4, 8, 4, 2>(Bt, n1, ldb, hc, W, Y, s);
+    }
+  if (n2 <= 0) return;
+  Bt += n1;
+  Y += n1 * hc.Kp;
+  if (tiles32(hc, n2) < kTinyTiles) launch_gemm_small(Bt, n2, ldb, hc, W, Y, s);
+  else launch_gemm<2, 2, 8>(Bt, n2, ldb, hc, W, Y, s);
 }
 
 void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
                          int variant, hipEvent_t mid) {
   const int64_t own = gemm_own_rows(hc, nb);
-  if (own < nb) launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s);
+  if (own < nb) launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s, variant);
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
   if (own > 0) launch_rows_gemm_fp64(c, hc, params, ld, b0, own, nodes, W, Y, s);
   if (own < nb) launch_gemm_fp64(Bt, nb - own, hc, W, Y + own * hc.Kp, s, variant);

@@ -142,7 +142,7 @@ static void eval_lnl_gemm(Ctx &c, const double *params, int64_t ld, int64_t n, d
       }
     mark(0);
     launch_epi_setup(c.consts.p, params, ld, b0, nb, c.epi_su.p, s);
-    launch_rows_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.Bt.p, s);
+    launch_rows_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.Bt.p, s, -1);
     mark(1);
     launch_gemm_lnl_fp64(c.Bt.p, nb, c.host_consts, c.W.p, c.consts.p, c.epi_su.p, c.basis4.p, c.coldesc.p,
                          c.epi_part.p, c.cap, s);

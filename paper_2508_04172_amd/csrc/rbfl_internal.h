@@ -362,7 +362,7 @@ void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
                          int variant, hipEvent_t mid);
 void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s);
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant);
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
                       int variant);
 void launch_contract_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
@@ -382,8 +382,9 @@ void launch_ragged_rows_fp64(const EventDesc *ev, int n_ev, int64_t total_groups
                              const double *params, int64_t ld, hipStream_t s);
 void launch_ragged_gemm_fp64(int variant, const EventDesc *ev, int n_ev, int64_t total_items,
                              unsigned long long *counter, int grid, hipStream_t s);
-// Small-batch tile of a multi-event batch by its count of 32 x 32 output tiles
-// (0: the variant's own), and the contraction with it, one workgroup per item.
+// Smaller tile that a multi-event batch of this count of 32 x 32 output tiles
+// takes in place of its variant's: 1 = 32 x 32, 2 = 64 x 64, 0 = none; and the
+// contraction with it, one workgroup per item.
 int ragged_small_tile(int64_t tiles);
 void launch_ragged_gemm_small_fp64(int small, const EventDesc *ev, int n_ev, int64_t total_items, hipStream_t s);
 void ragged_tile(int variant, int *proposals_per_tile, int *columns_per_tile);

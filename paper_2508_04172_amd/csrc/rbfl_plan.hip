@@ -117,8 +117,7 @@ static void plan_layout(Plan &p, int v, hipStream_t s) {
   int qt, cw;
   ragged_tile(v, &qt, &cw);
   const int n_ev = (int)p.ctx.size();
-  // a small batch takes the small tiles of the single-event contraction in
-  // place of the variant's (the same bits), one workgroup per item
+  // a small batch takes smaller tiles in place of the variant's (the same bits)
   p.small = 0;
   if (v >= ragged_fused_variants()) {
     int64_t tiles = 0;
@@ -274,7 +273,7 @@ static void plan_run(Plan &p, hipStream_t s) {
       launch_ragged_gemm_small_fp64(p.small, p.ev_work.p, n_ev, p.total_items, s);
     else
       launch_ragged_gemm_fp64(p.variant - ragged_fused_variants(), p.ev_work.p, n_ev, p.total_items, p.counter.p,
-                            p.grid, s);
+                              p.grid, s);
   }
   launch_ragged_epilogue(p.ev_param.p, n_ev, p.params, p.total, p.lnl, s);
 }
