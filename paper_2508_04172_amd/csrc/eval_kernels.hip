@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(kThreads) k_contract_fp32(const EvalConsts *__
 // additions.
 
 // ln L of one proposal from its setup o and interpolated row y; one whole
-// wave per call, result written to *out by lane 0.  The loads of each stage
+// wave per call, result in lane 0.  The loads of each stage
 // are issued together before their values are used (kEpiUnroll coefficients
 // per lane at a time, the detector's overlap reals one per lane), so a
 // proposal waits for a few memory round trips instead of one per coefficient.
@@ -234,14 +234,11 @@ constexpr int kEpiUnroll = 2;
 // coef_off / sig_off: the output offsets of the consts (an LDS copy where the
 // block has one).
 template <int U = kEpiUnroll>
-__device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &o, const double *__restrict__ y,
-                                           const double2 *__restrict__ basis4, double *__restrict__ out,
-                                           const int (*coef_off)[RBFL_MAX_MODES], const int *sig_off) {
+__device__ __forceinline__ double epi_reduce(const EvalConsts &c, const EpiSetup &o, const double *__restrict__ y,
+                                             const double2 *__restrict__ basis4,
+                                             const int (*coef_off)[RBFL_MAX_MODES], const int *sig_off) {
   const int lane = threadIdx.x & 63;
-  if (o.status != 0) {
-    if (lane == 0) *out = o.status == 2 ? __builtin_nan("") : -__builtin_huge_val();
-    return;
-  }
+  if (o.status != 0) return o.status == 2 ? __builtin_nan("") : -__builtin_huge_val();
   const int n_modes = c.n_modes, q = c.q, T = c.T;
   const int P = c.n_det * n_modes;
   const int G = 64 / P;
@@ -343,15 +340,17 @@ __device__ __forceinline__ void epi_reduce(const EvalConsts &c, const EpiSetup &
     comp += fabs(tot) >= fabs(v) ? (tot - t) + v : (v - t) + tot;
     tot = t;
   }
-  if (lane == 0) *out = tot + comp;
+  return tot + comp;
 }
 
-// EB proposals per workgroup, U coefficients in flight per lane.
+// EB proposals per workgroup, U coefficients in flight per lane.  nan, when
+// given: slot i gets 1 where ln L of proposal i is a NaN, else 0.
 template <int EB, int U>
 __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restrict__ cp,
                                                        const double *__restrict__ params, int64_t ld, int64_t b0,
                                                        int64_t nb, const double *__restrict__ Y,
-                                                       const double2 *__restrict__ basis4, double *__restrict__ lnl) {
+                                                       const double2 *__restrict__ basis4, double *__restrict__ lnl,
+                                                       NanCount *__restrict__ nan) {
   __shared__ EpiSetup su[EB];
   __shared__ EpiTmp tmp[EB];
   __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
@@ -375,8 +374,13 @@ __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restr
   const int nm = c.n_modes;
   epi_setup_block([&](int) -> const EvalConsts & { return c; }, [&](int, int i) -> const YlmTerms & { return ylm[i]; },
                   c.n_det, nm, params, ld, b0 + first, cnt, su, tmp);
-  for (int j = threadIdx.x >> 6; j < cnt; j += kWaves)
-    epi_reduce<U>(c, su[j], Y + (first + j) * c.Kp, basis4, lnl + b0 + first + j, coef_off, sig_off);
+  if (nan && blockIdx.x == 0 && threadIdx.x == 0) nan->slots = (unsigned)nb;
+  for (int j = threadIdx.x >> 6; j < cnt; j += kWaves) {
+    const double v = epi_reduce<U>(c, su[j], Y + (first + j) * c.Kp, basis4, coef_off, sig_off);
+    if ((threadIdx.x & 63) != 0) continue;
+    lnl[b0 + first + j] = v;
+    if (nan) nan->part[first + j] = isnan(v) ? 1u : 0u;
+  }
 }
 
 // Adds v to the compensated (Neumaier) sum (s, c).
@@ -403,17 +407,24 @@ __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *
                                                               const double *__restrict__ params, int64_t ld,
                                                               int64_t b0, int64_t nb, const double *__restrict__ Y,
                                                               const double2 *__restrict__ basis4,
-                                                              double *__restrict__ lnl) {
+                                                              double *__restrict__ lnl, NanCount *__restrict__ nan) {
   __shared__ double Ar[kWaves][kMaxPairs], Ai[kWaves][kMaxPairs], F[kWaves][kMaxPairs];
   __shared__ int N0[kWaves][kMaxPairs];
   const EvalConsts &c = *cp;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t g = (int64_t)blockIdx.x * kWaves + wave;
   if (g >= nb) return;   // whole wave leaves together (LDS is per wave: no block barriers)
+  auto put = [&](double v) {
+    if (lane != 0) return;
+    lnl[b0 + g] = v;
+    if (!nan) return;
+    nan->part[g] = isnan(v) ? 1u : 0u;
+    if (g == 0) nan->slots = (unsigned)nb;
+  };
   double p[11];
   const int pre = epi_prelude(c, params, ld, b0 + g, p);
   if (pre != 0) {   // NaN input, or outside the ellipsoid or the physical region
-    if (lane == 0) lnl[b0 + g] = pre == 2 ? __builtin_nan("") : -__builtin_huge_val();
+    put(pre == 2 ? __builtin_nan("") : -__builtin_huge_val());
     return;
   }
   const double alpha = p[4], dec = p[5], psi = p[6], iota = p[7], phi = p[8], tc = p[9], dl = p[10];
@@ -444,7 +455,7 @@ __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *
     F[wave][pr] = s - fl;
   }
   if (!__all(ok ? 1 : 0)) {
-    if (lane == 0) lnl[b0 + g] = -__builtin_huge_val();
+    put(-__builtin_huge_val());
     return;
   }
   double sum = 0.0, comp = 0.0;
@@ -513,7 +524,7 @@ __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *
     comp += c2;
     comp_add(sum, comp, s2);
   }
-  if (lane == 0) lnl[b0 + g] = sum + comp;
+  put(sum + comp);
 }
 
 // Epilogue finished inside the contraction (FP64 form, optional): ln L is
@@ -659,14 +670,16 @@ __global__ void __launch_bounds__(kThreads) k_ragged_epilogue(const EventDesc *_
   for (int j = threadIdx.x >> 6; j < cnt; j += kWaves) {
     const int64_t g = first + j;
     const EventDesc &d = ev[su[j].event];
-    epi_reduce<>(*d.consts, su[j], d.Y + (g - d.q0) * d.Kp, d.basis, lnl + g, d.consts->coef_off, d.consts->sig_off);
+    const double v =
+        epi_reduce<>(*d.consts, su[j], d.Y + (g - d.q0) * d.Kp, d.basis, d.consts->coef_off, d.consts->sig_off);
+    if ((threadIdx.x & 63) == 0) lnl[g] = v;
   }
 }
 
 // NaN entries of lnl[0, n): block b writes its grid-stride share's count to
-// part[b] (every block writes, so the slots need no clearing).
+// slot b (every block writes, so the slots need no clearing).
 __global__ void __launch_bounds__(256) k_count_nan(const double *__restrict__ lnl, int64_t n,
-                                                   unsigned long long *__restrict__ part) {
+                                                   NanCount *__restrict__ nan) {
   __shared__ unsigned long long cnt;
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
@@ -675,7 +688,9 @@ __global__ void __launch_bounds__(256) k_count_nan(const double *__restrict__ ln
     mine += isnan(lnl[i]) ? 1ull : 0ull;
   if (mine) atomicAdd(&cnt, mine);
   __syncthreads();
-  if (threadIdx.x == 0) part[blockIdx.x] = cnt;
+  if (threadIdx.x != 0) return;
+  nan->part[blockIdx.x] = cnt;
+  if (blockIdx.x == 0) nan->slots = gridDim.x;
 }
 
 // Surrogate inputs: x = delta_e / a in FP32, [nb][4].
@@ -875,26 +890,32 @@ constexpr int64_t kEpiSmall = 4096, kEpiLarge = 32768;
 
 template <int EB, int U>
 static void launch_epilogue_variant(const EvalConsts *c, const double *params, int64_t ld, int64_t b0, int64_t nb,
-                                    const double *Y, const double2 *basis, double *lnl, hipStream_t s) {
+                                    const double *Y, const double2 *basis, double *lnl, hipStream_t s, NanCount *nan) {
   hipLaunchKernelGGL((k_epilogue<EB, U>), dim3((unsigned)((nb + EB - 1) / EB)), dim3(kThreads), 0, s, c, params, ld,
-                     b0, nb, Y, basis, lnl);
+                     b0, nb, Y, basis, lnl, nan);
 }
 
-void launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                     int64_t nb, const double *Y, const double2 *basis, double *lnl, hipStream_t s) {
-  if (nb <= 0) return;
+// nan, when given, is filled by the epilogue where the batch fits its slots (a
+// launch of its own costs a small batch 2-5 us, of 62 us at 1021 proposals).
+// Returns whether it was.
+bool launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                     int64_t nb, const double *Y, const double2 *basis, double *lnl, hipStream_t s, NanCount *nan) {
+  static_assert(kEpiSmall <= kNanSlots, "one slot per proposal");
+  if (nb <= 0) return false;
+  if (nb > kEpiSmall) nan = nullptr;
   if (hc.n_bands > 1) {
     hipLaunchKernelGGL(k_epilogue_banded, dim3((unsigned)((nb + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, c,
-                       params, ld, b0, nb, Y, basis, lnl);
+                       params, ld, b0, nb, Y, basis, lnl, nan);
   } else {
     if (nb <= kEpiSmall)
-      launch_epilogue_variant<4, 5>(c, params, ld, b0, nb, Y, basis, lnl, s);
+      launch_epilogue_variant<4, 5>(c, params, ld, b0, nb, Y, basis, lnl, s, nan);
     else if (nb > kEpiLarge && hc.n_det * hc.n_modes <= 4)
-      launch_epilogue_variant<32, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s);
+      launch_epilogue_variant<32, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s, nan);
     else
-      launch_epilogue_variant<16, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s);
+      launch_epilogue_variant<16, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s, nan);
   }
   RBFL_HIP(hipGetLastError());
+  return nan != nullptr;
 }
 
 size_t epi_setup_bytes() { return sizeof(EpiSetup); }
@@ -922,8 +943,10 @@ void launch_series_lnl(const EvalConsts *c, const double *params, int64_t ld, in
   RBFL_HIP(hipGetLastError());
 }
 
-void launch_count_nan(const double *lnl, int64_t n, unsigned long long *part, hipStream_t s) {
-  hipLaunchKernelGGL(k_count_nan, dim3(kNanParts), dim3(256), 0, s, lnl, n, part);
+void launch_count_nan(const double *lnl, int64_t n, NanCount *nan, hipStream_t s) {
+  constexpr int kBlocks = 256;
+  static_assert(kBlocks <= kNanSlots, "one slot per block");
+  hipLaunchKernelGGL(k_count_nan, dim3(kBlocks), dim3(256), 0, s, lnl, n, nan);
   RBFL_HIP(hipGetLastError());
 }
 

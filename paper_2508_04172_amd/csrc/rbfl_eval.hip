@@ -192,25 +192,29 @@ static void eval_split_lnl(Ctx &c, const double *params, int64_t ld, int64_t n, 
   }
 }
 
-// ln L of proposals [0, n) of a parameter array with leading dimension ld.
-static void eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, double *lnl, int form, hipStream_t s) {
-  if (n == 0) return;
+// ln L of proposals [0, n) of a parameter array with leading dimension ld;
+// whether their NaN results have been counted too (into nan, when given).
+static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, double *lnl, int form, hipStream_t s,
+                       NanCount *nan = nullptr) {
+  if (n == 0) return false;
   if (c.cap == 0) reserve(c, std::min<int64_t>(n, 65536));
   const bool fp64 = form == RBFL_FORM_FP64 || (form == RBFL_FORM_SURROGATE && !(c.sur && c.sur_ok));
   if (fp64 && c.lnl_gemm) {
     eval_lnl_gemm(c, params, ld, n, lnl, s);
-    return;
+    return false;
   }
   if (form == RBFL_FORM_SPLIT && c.split_lnl) {
     eval_split_lnl(c, params, ld, n, lnl, s);
-    return;
+    return false;
   }
   if (fp64 && c.pipe > 1 && c.cap / 2 >= 4096 && n > 4096 && !capturing(s)) {
     eval_pipelined(c, params, ld, n, lnl, s);
-    return;
+    return false;
   }
+  bool counted = false;
   for (int64_t b0 = 0; b0 < n; b0 += c.cap) {
     const int64_t nb = std::min(c.cap, n - b0);
+    if (nb < n) nan = nullptr;
     if (c.profile) {
       // stages: basis rows (kind 2), MFMA contraction (kind 0), epilogue (kind 1)
       hipEvent_t ev[4];
@@ -219,7 +223,7 @@ static void eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
         c.timed_events.push_back(e);
       }
       contract(c, params, ld, b0, nb, form, s, ev);
-      launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s);
+      counted = launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
       RBFL_HIP(hipEventRecord(ev[3], s));
       c.timed.push_back(Ctx::Timed{ev[0], ev[1], 2, nb});
       c.timed.push_back(Ctx::Timed{ev[1], ev[2], 0, nb});
@@ -227,8 +231,9 @@ static void eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
       continue;
     }
     contract(c, params, ld, b0, nb, form, s);
-    launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s);
+    counted = launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
   }
+  return counted;
 }
 
 void eval(Ctx &c, const double *params, int64_t n, double *lnl, int form, hipStream_t s) {
@@ -236,8 +241,7 @@ void eval(Ctx &c, const double *params, int64_t n, double *lnl, int form, hipStr
   require(n >= 0, "n must be >= 0");
   if (form < 0 || form > RBFL_FORM_SURROGATE) throw Error(RBFL_E_INVALID_ARG, "unknown form");
   if (!c.prepared[form]) throw Error(RBFL_E_STATE, "form not prepared (call rbfl_prepare)");
-  eval_range(c, params, n, n, lnl, form, s);
-  launch_count_nan(lnl, n, c.nan_part.p, s);
+  if (!eval_range(c, params, n, n, lnl, form, s, c.nan.p)) launch_count_nan(lnl, n, c.nan.p, s);
 }
 
 // The contraction of proposals [b0, b0 + nb) into the work space Y, in two

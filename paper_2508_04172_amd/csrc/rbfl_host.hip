@@ -1437,8 +1437,8 @@ static void build_back(const rbfl_build_spec *s, hipStream_t stream, Ctx &c, Bui
   RBFL_HIP(hipMemcpyAsync(c.consts.p, &e, sizeof(e), hipMemcpyHostToDevice, stream));
   c.basis4.alloc((size_t)c.n_v * c.n_modes * c.T * c.q * 4);
   launch_fold_spline(c.basis.p, c.n_v * c.n_modes, c.T, c.q, c.consts.p, c.basis4.p, stream);
-  c.nan_part.alloc(kNanParts);
-  launch_count_nan(nullptr, 0, c.nan_part.p, stream);
+  c.nan.alloc(1);
+  launch_count_nan(nullptr, 0, c.nan.p, stream);
   RBFL_HIP(hipStreamSynchronize(stream));
   c.timing[5] = seconds_since(carry.t_all);
   if (debug_mode()) debug_check_layout(c);

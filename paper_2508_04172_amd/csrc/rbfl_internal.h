@@ -178,9 +178,14 @@ struct Mlp {
   void adam(double lr, double b1, double b2, double eps, hipStream_t s);
 };
 
-// Partial counts of NaN ln L values of the last evaluation call (one per
-// block of the counting kernel, summed by rbfl_query).
-constexpr int kNanParts = 256;
+// NaN ln L values of the last evaluation call: `slots` partial counts, one per
+// block of the counting kernel or, in a small batch, one per proposal; each
+// call writes all that it announces, rbfl_query sums them.
+constexpr int kNanSlots = 4096;
+struct NanCount {
+  unsigned long long slots;
+  unsigned long long part[kNanSlots];
+};
 
 struct Ctx {
   int device = 0;              // the device current at rbfl_build / rbfl_load; every artefact lives there
@@ -217,7 +222,7 @@ struct Ctx {
   int64_t brute_j_lo = 0, brute_J = 0;
   DevBuf<double2> win_D;       // exact outputs: brute_D with the window start's phase, made on first use
   DevBuf<int4> coldesc;        // output column layout (kind, detector, mode, index), [K]
-  DevBuf<unsigned long long> nan_part;   // [kNanParts] NaN counts of the last evaluation call
+  DevBuf<NanCount> nan;        // of the last evaluation call
   // reduced-precision weight copies
   DevBuf<float> W32;           // [rows][Kp]
   DevBuf<uint16_t> W16;        // BF16 form: weights in 8-row groups [rows/8][Kp][8]
@@ -392,8 +397,8 @@ void launch_ragged_contract(int variant, const EventDesc *ev, int n_ev, int64_t 
                             unsigned long long *counter, const double *params, int64_t ld, int grid, hipStream_t s);
 void launch_ragged_epilogue(const EventDesc *ev, int n_ev, const double *params, int64_t total, double *lnl,
                             hipStream_t s);
-void launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                     int64_t nb, const double *Y, const double2 *basis, double *lnl, hipStream_t s);
+bool launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                     int64_t nb, const double *Y, const double2 *basis, double *lnl, hipStream_t s, NanCount *nan = nullptr);
 // Epilogue inside the FP64 contraction: per-proposal setups (epi_setup_bytes()
 // each), the contraction's partial sums part[column tile][ldp], their sum.
 size_t epi_setup_bytes();
@@ -436,9 +441,8 @@ void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *p
                       int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
                       const double *cscale, const void *setups, const double2 *basis4, const int4 *coldesc,
                       double *part, int64_t ldp, hipStream_t s, int variant, hipEvent_t mid);
-// part[b] = number of NaN entries of lnl[0, n) in block b's grid-stride share
-// (kNanParts blocks; every slot is written, so no clearing is needed).
-void launch_count_nan(const double *lnl, int64_t n, unsigned long long *part, hipStream_t s);
+// The NaN entries of lnl[0, n), one partial count per block.
+void launch_count_nan(const double *lnl, int64_t n, NanCount *nan, hipStream_t s);
 // The nbase monomials (graded-lexicographic, variable indices poly[p][0..2],
 // -1 unused) of u = (x - ms[0..3]) / ms[4..7], x = delta_e / a, in FP64:
 // U[b][p] for proposals b0 .. b0 + nb - 1.

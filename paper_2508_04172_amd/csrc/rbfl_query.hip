@@ -155,11 +155,11 @@ void query(Ctx &c, int what, void *out, size_t bytes) {
     }
     case RBFL_Q_NAN_COUNT: {
       require(out != nullptr && bytes >= sizeof(int64_t), "output buffer too small (need 8 bytes)");
-      unsigned long long part[kNanParts];
+      NanCount nan;
       RBFL_HIP(hipDeviceSynchronize());
-      RBFL_HIP(hipMemcpy(part, c.nan_part.p, sizeof(part), hipMemcpyDeviceToHost));
+      RBFL_HIP(hipMemcpy(&nan, c.nan.p, sizeof(nan), hipMemcpyDeviceToHost));
       int64_t total = 0;
-      for (int i = 0; i < kNanParts; ++i) total += (int64_t)part[i];
+      for (unsigned long long i = 0; i < nan.slots; ++i) total += (int64_t)nan.part[i];
       std::memcpy(out, &total, sizeof(total));
       return;
     }

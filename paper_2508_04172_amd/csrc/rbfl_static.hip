@@ -66,6 +66,7 @@ void eval_static(Ctx &c, const double *params, int64_t n, double *lnl, hipStream
   double *Y = static_cast<double *>(scratch_on(dev));
   double *Bt = Y + (size_t)chunk * c.Kp;   // rows x rows_ld(nb) <= rows x chunk doubles
   const int v = c.variant[RBFL_FORM_FP64];
+  bool counted = false;
   for (int64_t b0 = 0; b0 < n; b0 += chunk) {
     const int64_t nb = std::min(chunk, n - b0);
     if (v < gemm_fp64_variants()) {
@@ -73,9 +74,10 @@ void eval_static(Ctx &c, const double *params, int64_t n, double *lnl, hipStream
     } else {
       launch_contract_fp64(c.consts.p, c.host_consts, params, n, b0, nb, c.nodes.p, c.W.p, Y, s, 2);
     }
-    launch_epilogue(c.consts.p, c.host_consts, params, n, b0, nb, Y, c.basis4.p, lnl, s);
+    counted = launch_epilogue(c.consts.p, c.host_consts, params, n, b0, nb, Y, c.basis4.p, lnl, s,
+                              nb == n ? c.nan.p : nullptr);
   }
-  launch_count_nan(lnl, n, c.nan_part.p, s);
+  if (!counted) launch_count_nan(lnl, n, c.nan.p, s);
 }
 
 }  // namespace

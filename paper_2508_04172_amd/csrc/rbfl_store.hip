@@ -395,8 +395,8 @@ void load(const char *path, hipStream_t st, Ctx &c) {
   upload(c.brute_D, bd, st);
   upload(c.brute_w, bw, st);
   upload(c.coldesc, cd, st);
-  c.nan_part.alloc(kNanParts);
-  launch_count_nan(nullptr, 0, c.nan_part.p, st);
+  c.nan.alloc(1);
+  launch_count_nan(nullptr, 0, c.nan.p, st);
   RBFL_HIP(hipStreamSynchronize(st));
   if (debug_mode()) debug_check_layout(c);
 }

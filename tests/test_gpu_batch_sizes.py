@@ -57,6 +57,19 @@ def test_batch_size(case, n):
     assert fin.sum() == 0 or np.abs(got[fin] - want[fin]).max() <= 1e-8
 
 
+# up to 4096 proposals the epilogue counts the NaN results itself, one slot each
+@pytest.mark.parametrize("n", [1, 5, 4096, 4097])
+def test_nan_count(case, n):
+    h, p, _, _ = case
+    sub = p[:, :n].contiguous()
+    lnl(h, sub)
+    assert h.nan_count() == 0
+    bad = sorted({0, n // 2, n - 1})
+    sub[8, bad] = float("nan")
+    assert np.flatnonzero(np.isnan(lnl(h, sub))).tolist() == bad
+    assert h.nan_count() == len(bad)
+
+
 # 2 column tiles of 128: rounds of 128 (256 x 128) and 256 (128 x 128) tiles along
 # the proposals; 90,000 are 2.75 and 2.75 of them, 100,000 3.06, 110,000 3.36
 @pytest.mark.parametrize("n", [90_000, 99_999, N_ALL])
