@@ -224,125 +224,6 @@ __global__ void __launch_bounds__(kThreads) k_contract_fp32(const EvalConsts *__
 // first lane the overlap term, lane 0 the sum, all with compensated (Neumaier)
 // additions.
 
-// ln L of one proposal from its setup o and interpolated row y; one whole
-// wave per call, result in lane 0.  The loads of each stage
-// are issued together before their values are used (kEpiUnroll coefficients
-// per lane at a time, the detector's overlap reals one per lane), so a
-// proposal waits for a few memory round trips instead of one per coefficient.
-constexpr int kEpiUnroll = 2;
-
-// coef_off / sig_off: the output offsets of the consts (an LDS copy where the
-// block has one).
-template <int U = kEpiUnroll>
-__device__ __forceinline__ double epi_reduce(const EvalConsts &c, const EpiSetup &o, const double *__restrict__ y,
-                                             const double2 *__restrict__ basis4,
-                                             const int (*coef_off)[RBFL_MAX_MODES], const int *sig_off) {
-  const int lane = threadIdx.x & 63;
-  if (o.status != 0) return o.status == 2 ? __builtin_nan("") : -__builtin_huge_val();
-  const int n_modes = c.n_modes, q = c.q, T = c.T;
-  const int P = c.n_det * n_modes;
-  const int G = 64 / P;
-  const int pair = lane / G;
-  const int gl = lane - pair * G;
-  const bool active = pair < P;
-  const int k = active ? pair / n_modes : 0;
-  const int a = active ? pair - k * n_modes : 0;
-  const double f = o.f[k];
-  const int n0 = o.n0[k];
-  const double ar = o.Ar[k][a], ai = o.Ai[k][a];
-  const int det_lead = k * n_modes * G;
-  // detector k's overlap reals: lane det_lead + t holds term t (t < n_modes:
-  // sigma_tt; then (Re, Im) sigma_ab for a < b in lexicographic order).  A
-  // detector owns n_modes * G >= n_modes (n_modes + 1) / 2 lanes for up to 4
-  // detectors and 5 modes.
-  const int n_terms = n_modes * (n_modes + 1) / 2;
-  const int t_own = lane - det_lead;
-  double sg_a = 0.0, sg_b = 0.0;
-  if (active && t_own < n_terms) {
-    const int so = sig_off[k];
-    if (t_own < n_modes) {
-      sg_a = y[so + t_own];
-    } else {
-      const int pidx = so + n_modes + 2 * (t_own - n_modes);
-      sg_a = y[pidx];
-      sg_b = y[pidx + 1];
-    }
-  }
-  // a5: partial reconstruction of z_{k,a} over this lane's coefficients; the
-  // spline-folded basis gives the interpolated basis value as a cubic in f
-  double zr = 0.0, zi = 0.0;
-  if (active) {
-    const int off = coef_off[k][a];
-    const double2 *base = basis4 + ((int64_t)(k * n_modes + a) * T + n0) * q * 4;
-    for (int i0 = gl; i0 < q; i0 += U * G) {
-      double2 cc[U], v[U][4];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // past the end: a valid entry is loaded and its coefficient zeroed,
-        // so that every load is issued before the first use
-        const bool ok = i0 + u * G < q;
-        const int i = ok ? i0 + u * G : i0;
-        const double2 cv = *reinterpret_cast<const double2 *>(y + off + 2 * i);
-        cc[u].x = ok ? cv.x : 0.0;
-        cc[u].y = ok ? cv.y : 0.0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[u][j] = base[4 * i + j];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const double br = fma(fma(fma(v[u][3].x, f, v[u][2].x), f, v[u][1].x), f, v[u][0].x);
-        const double bi = fma(fma(fma(v[u][3].y, f, v[u][2].y), f, v[u][1].y), f, v[u][0].y);
-        zr += cc[u].x * br - cc[u].y * bi;
-        zi += cc[u].x * bi + cc[u].y * br;
-      }
-    }
-  }
-  // combine the G partials of each pair in its first lane (a fixed tree: after
-  // the step of distance o, lane g of a pair holds the sum over lanes
-  // g .. g + 2 o - 1 of it)
-  double tr = zr, ti = zi;
-  for (int o = 1; o < G; o <<= 1) {
-    const double vr = __shfl(tr, lane + o, 64), vi = __shfl(ti, lane + o, 64);
-    if (gl + o < G) {
-      tr += vr;
-      ti += vi;
-    }
-  }
-  const double zterm = ar * tr + ai * ti;   // Re(conj(A) z), valid in pair leaders
-  // overlap term of detector k: every A_{k,b} is in the setup
-  double st_s = 0.0, st_c = 0.0, zt_s = 0.0, zt_c = 0.0;
-  {
-    auto add = [](double &sum, double &comp, double v) {
-      const double t = sum + v;
-      comp += fabs(sum) >= fabs(v) ? (sum - t) + v : (v - t) + sum;
-      sum = t;
-    };
-    for (int m = 0; m < n_modes; ++m) {
-      add(zt_s, zt_c, __shfl(zterm, det_lead + m * G, 64));
-      add(st_s, st_c, (o.Ar[k][m] * o.Ar[k][m] + o.Ai[k][m] * o.Ai[k][m]) * __shfl(sg_a, det_lead + m, 64));
-    }
-    int t = n_modes;
-    for (int m = 0; m < n_modes; ++m)
-      for (int mm = m + 1; mm < n_modes; ++mm) {
-        const double sr = __shfl(sg_a, det_lead + t, 64), si = __shfl(sg_b, det_lead + t, 64);
-        ++t;
-        const double pr = o.Ar[k][m] * o.Ar[k][mm] + o.Ai[k][m] * o.Ai[k][mm];
-        const double pi = o.Ar[k][m] * o.Ai[k][mm] - o.Ai[k][m] * o.Ar[k][mm];
-        add(st_s, st_c, 2.0 * (pr * sr - pi * si));
-      }
-  }
-  const double rr = o.rr;
-  const double term = rr * (zt_s + zt_c) - 0.5 * rr * rr * (st_s + st_c);   // valid in detector leaders
-  double tot = 0.0, comp = 0.0;
-  for (int kk = 0; kk < c.n_det; ++kk) {
-    const double v = __shfl(term, kk * n_modes * G, 64);
-    const double t = tot + v;
-    comp += fabs(tot) >= fabs(v) ? (tot - t) + v : (v - t) + tot;
-    tot = t;
-  }
-  return tot + comp;
-}
-
 // EB proposals per workgroup, U coefficients in flight per lane.  nan, when
 // given: slot i gets 1 where ln L of proposal i is a NaN, else 0.
 template <int EB, int U>

@@ -207,6 +207,16 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
     eval_split_lnl(c, params, ld, n, lnl, s);
     return false;
   }
+  // the smallest batches in one launch (not where the stages are timed, nor
+  // with the tile that forms its rows in registers)
+  if (fp64 && nan && !c.profile && n <= c.cap && c.variant[RBFL_FORM_FP64] < gemm_fp64_variants()) {
+    const int slots = small_eval_group(c.host_consts, n);
+    if (slots > 0) {
+      launch_eval_small(slots, c.consts.p, c.host_consts, params, ld, n, c.nodes.p, c.W.p, c.Y.p, c.basis4.p, lnl,
+                        nan, c.small_done.p, s);
+      return true;
+    }
+  }
   if (fp64 && c.pipe > 1 && c.cap / 2 >= 4096 && n > 4096 && !capturing(s)) {
     eval_pipelined(c, params, ld, n, lnl, s);
     return false;

@@ -223,6 +223,7 @@ struct Ctx {
   DevBuf<double2> win_D;       // exact outputs: brute_D with the window start's phase, made on first use
   DevBuf<int4> coldesc;        // output column layout (kind, detector, mode, index), [K]
   DevBuf<NanCount> nan;        // of the last evaluation call
+  DevBuf<unsigned> small_done; // [kSmallBlocks / 2] finished workgroups of a one-launch evaluation, 0 between calls
   // reduced-precision weight copies
   DevBuf<float> W32;           // [rows][Kp]
   DevBuf<uint16_t> W16;        // BF16 form: weights in 8-row groups [rows/8][Kp][8]
@@ -441,6 +442,14 @@ void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *p
                       int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
                       const double *cscale, const void *setups, const double2 *basis4, const int4 *coldesc,
                       double *part, int64_t ldp, hipStream_t s, int variant, hipEvent_t mid);
+// FP64 ln L of n proposals in one launch (eval_small.hip), `slots` =
+// small_eval_group(n) of them per workgroup (0: n is too large); done[kSmallBlocks
+// / 2] holds zeros between the launches, nan is filled too.
+constexpr int kSmallBlocks = 256;
+int small_eval_group(const EvalConsts &hc, int64_t n);
+void launch_eval_small(int slots, const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
+                       int64_t n, const double *nodes, const double *W, double *Y, const double2 *basis4, double *lnl,
+                       NanCount *nan, unsigned *done, hipStream_t s);
 // The NaN entries of lnl[0, n), one partial count per block.
 void launch_count_nan(const double *lnl, int64_t n, NanCount *nan, hipStream_t s);
 // The nbase monomials (graded-lexicographic, variable indices poly[p][0..2],

@@ -40,8 +40,9 @@ def lnl(h, p):
 
 
 # 256 columns are 8 tiles of 32: the tiles change at 2880 / 8 and 22000 / 8 rows
-# of 32 proposals, the epilogue at 4096 proposals; remainders of 16, 32 and 64
-@pytest.mark.parametrize("n", [1, 2, 15, 17, 33, 63, 65, 1021, 4096, 4097, 11487, 11489, 12289, 65505, 87967, 87969])
+# of 32 proposals, the epilogue at 4096 proposals; remainders of 16, 32 and 64.
+# Up to 1024 proposals (64 groups of at most 16) ln L is one launch.
+@pytest.mark.parametrize("n", [1, 2, 15, 17, 33, 63, 65, 1021, 1024, 1025, 4096, 4097, 11487, 11489, 12289, 65505, 87967, 87969])
 def test_batch_size(case, n):
     import torch
     h, p, ref, ref_lnl = case
@@ -135,3 +136,34 @@ def test_one_column_tile(nodes, n):
     got = interp(h, p)
     for b in range(0, n, 8192):
         assert torch.equal(interp(h, p[:, b:b + 8192].contiguous()), got[b:b + 8192])
+
+
+# one launch against the staged kernels (which the stage timers keep): columns
+# 128 / 512, rows 96 / 320, so 1 to 16 proposals per workgroup, ragged last
+# groups, and the sizes around the largest that takes one launch
+@pytest.mark.parametrize("sites, modes, nodes, degree, q, sizes", [
+    (1, 1, 60, 1, 5, [1, 2, 127, 128, 129, 255, 257, 1000, 2033, 2048, 2049]),
+    (1, 2, 150, 3, 13, [1, 3, 65, 511]),
+    (3, 4, 300, 2, 16, [1, 31, 32, 33, 100, 255, 481, 512, 513]),
+])
+def test_one_launch(sites, modes, nodes, degree, q, sizes):
+    import torch
+    cfg = wl.SMALL_MULTI.with_(name="one_launch", sites=wl.SITES_HLV[:sites], modes=wl.ALL_MODES[:modes], n_nodes=nodes,
+                               poly_degree=degree, q=q, eps=0.0)
+    h = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    n_all = max(sizes)
+    idx, jit = wl.node_jitter(n_all, cfg.n_nodes)
+    qd = wl.queries(cfg, n=n_all).near_nodes(h.nodes(), idx, jit)
+    P = np.ascontiguousarray(rbfl.params_soa(h, qd, cfg.t_trig))
+    P[9, ::7] = cfg.t_trig + 10.0                     # outside the window
+    P[6, ::11] = np.nan
+    p = torch.from_numpy(P).cuda()
+    h.reserve(n_all)
+    for n in sizes:
+        sub = p[:, n_all - n:].contiguous()
+        h.profile(True)
+        want = lnl(h, sub)
+        h.profile(False)
+        for _ in range(2):                            # the second finds the counters that the first left
+            assert np.array_equal(lnl(h, sub), want, equal_nan=True)
+            assert h.nan_count() == int(np.isnan(want).sum())
