@@ -57,6 +57,16 @@ __global__ void __launch_bounds__(256) k_rows_fp64(const EvalConsts *__restrict_
   }
 }
 
+// Row r of proposal q (zero for q >= nb).
+__device__ __forceinline__ double row_value(const EvalConsts &c, const double *__restrict__ params, int64_t ld,
+                                            int64_t b0, int nb, int r, int q, const double *__restrict__ nodes) {
+  if (q >= nb) return 0.0;
+  double x[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) x[d] = params[d * ld + b0 + q] / c.semi[d];
+  return basis_row_fp64(r, c.N, c.N + c.M, x, nodes + 4 * (int64_t)r, c.eps2, c.poly_idx);
+}
+
 // The same rows for small batches, one row value per thread (t = r ldb + q):
 // k_rows_fp64's 16 exponentials in a row per thread are a chain that a launch
 // of few workgroups waits for.
@@ -68,14 +78,37 @@ __global__ void __launch_bounds__(256) k_rows_small_fp64(const EvalConsts *__res
   const unsigned t = blockIdx.x * 256 + threadIdx.x;
   const unsigned r = t / (unsigned)ldb, q = t - r * (unsigned)ldb;
   if (r >= (unsigned)n_rows) return;
-  double v = 0.0;
-  if ((int)q < nb) {
-    double x[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) x[d] = params[d * ld + b0 + q] / c.semi[d];
-    v = basis_row_fp64((int)r, c.N, c.N + c.M, x, nodes + 4 * (int64_t)r, c.eps2, c.poly_idx);
+  Bt[(int64_t)r * ldb + q] = row_value(c, params, ld, b0, nb, (int)r, (int)q, nodes);
+}
+
+// k_rows_small_fp64 whose first n_setup workgroups form the setups of the
+// epilogue (kSetupGroup proposals each) instead: a chain of dependent steps that
+// the row values of the others hide.
+constexpr int kSetupGroup = 8;
+__global__ void __launch_bounds__(256) k_rows_setup_fp64(const EvalConsts *__restrict__ cp,
+                                                         const double *__restrict__ params, int64_t ld, int64_t b0,
+                                                         int nb, int ldb, int n_rows,
+                                                         const double *__restrict__ nodes, double *__restrict__ Bt,
+                                                         int n_setup, EpiSetup *__restrict__ setups) {
+  const EvalConsts &c = *cp;
+  if ((int)blockIdx.x < n_setup) {
+    __shared__ EpiSetup su[kSetupGroup];
+    __shared__ EpiTmp tmp[kSetupGroup];
+    __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
+    const int first = blockIdx.x * kSetupGroup, cnt = min(kSetupGroup, nb - first);
+    epi_copy_ylm(threadIdx.x, c, ylm);
+    __syncthreads();
+    epi_setup_block([&](int) -> const EvalConsts & { return c; },
+                    [&](int, int i) -> const YlmTerms & { return ylm[i]; }, c.n_det, c.n_modes, params, ld, b0 + first,
+                    cnt, su, tmp);
+    for (int e = threadIdx.x; e < cnt * (int)(sizeof(EpiSetup) / 8); e += 256)
+      reinterpret_cast<double *>(setups + first)[e] = reinterpret_cast<const double *>(su)[e];
+    return;
   }
-  Bt[(int64_t)r * ldb + q] = v;
+  const unsigned t = (blockIdx.x - n_setup) * 256 + threadIdx.x;
+  const unsigned r = t / (unsigned)ldb, q = t - r * (unsigned)ldb;
+  if (r >= (unsigned)n_rows) return;
+  Bt[(int64_t)r * ldb + q] = row_value(c, params, ld, b0, nb, (int)r, (int)q, nodes);
 }
 
 // Workgroups are dealt to the 8 XCDs in turn; this gives each XCD a
@@ -786,21 +819,30 @@ void launch_rows_gemm_fp64(const EvalConsts *c, const EvalConsts &hc, const doub
   RBFL_HIP(hipGetLastError());
 }
 
-void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant) {
+bool launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups) {
   const int64_t ldb = rows_ld(nb);
   const int n_rows = rows_needed(hc, nb, variant);
   // one value per thread while that is fewer than four rounds of the chip
   // (1021 proposals of 832 rows: 9.1 against 10.7 us; 2048: no gain)
   if (ldb * n_rows <= (1 << 20)) {
-    hipLaunchKernelGGL(k_rows_small_fp64, dim3((unsigned)((ldb * n_rows + 255) / 256)), dim3(256), 0, s, c, params, ld,
-                       b0, (int)nb, (int)ldb, n_rows, nodes, Bt);
+    const unsigned blocks = (unsigned)((ldb * n_rows + 255) / 256);
+    const bool with_setups = setups != nullptr && nb <= kSetupMax && hc.n_bands <= 1;
+    if (with_setups) {
+      const int n_setup = (int)((nb + kSetupGroup - 1) / kSetupGroup);
+      hipLaunchKernelGGL(k_rows_setup_fp64, dim3(n_setup + blocks), dim3(256), 0, s, c, params, ld, b0, (int)nb,
+                         (int)ldb, n_rows, nodes, Bt, n_setup, static_cast<EpiSetup *>(setups));
+    } else {
+      hipLaunchKernelGGL(k_rows_small_fp64, dim3(blocks), dim3(256), 0, s, c, params, ld, b0, (int)nb, (int)ldb, n_rows,
+                         nodes, Bt);
+    }
     RBFL_HIP(hipGetLastError());
-    return;
+    return with_setups;
   }
   dim3 grid((unsigned)((ldb + 255) / 256), (unsigned)(n_rows / 16));
   hipLaunchKernelGGL(k_rows_fp64, grid, dim3(256), 0, s, c, params, ld, b0, nb, ldb, nodes, Bt);
   RBFL_HIP(hipGetLastError());
+  return false;
 }
 
 void launch_ragged_rows_fp64(const EventDesc *ev, int n_ev, int64_t total_groups, int64_t max_ldb,
@@ -857,14 +899,17 @@ void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const 
   else launch_gemm<2, 2, 8>(Bt, n2, ldb, hc, W, Y, s);
 }
 
-void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+bool launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
-                         int variant, hipEvent_t mid) {
+                         int variant, hipEvent_t mid, void *setups) {
   const int64_t own = gemm_own_rows(hc, nb);
-  if (own < nb) launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s, variant);
+  bool ready = false;
+  if (own < nb)
+    ready = launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s, variant, own == 0 ? setups : nullptr);
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
   if (own > 0) launch_rows_gemm_fp64(c, hc, params, ld, b0, own, nodes, W, Y, s);
   if (own < nb) launch_gemm_fp64(Bt, nb - own, hc, W, Y + own * hc.Kp, s, variant);
+  return ready;
 }
 
 }  // namespace rbfl

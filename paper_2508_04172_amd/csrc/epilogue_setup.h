@@ -330,4 +330,23 @@ __device__ __forceinline__ double epi_reduce(const EvalConsts &c, const EpiSetup
   return tot + comp;
 }
 
+// The harmonics' terms of c, n_modes of -m, then n_modes of +m, into LDS by
+// threads t = 0 .. 255, word by word.
+__device__ __forceinline__ void epi_copy_ylm(int t, const EvalConsts &c, YlmTerms *ylm) {
+  constexpr int kWords = sizeof(YlmTerms) / 4;
+  static_assert(sizeof(YlmTerms) % 4 == 0, "copied by words");
+  const int words = c.n_modes * kWords;
+  for (int e = t; e < 2 * words; e += 256)
+    reinterpret_cast<int *>(ylm)[e] =
+        e < words ? reinterpret_cast<const int *>(c.ylm_neg)[e] : reinterpret_cast<const int *>(c.ylm_pos)[e - words];
+}
+
+// c's output offsets likewise.
+__device__ __forceinline__ void epi_copy_offsets(int t, const EvalConsts &c, int (*coef_off)[RBFL_MAX_MODES],
+                                                 int *sig_off) {
+  if (t >= RBFL_MAX_DET * RBFL_MAX_MODES) return;
+  coef_off[t / RBFL_MAX_MODES][t % RBFL_MAX_MODES] = c.coef_off[t / RBFL_MAX_MODES][t % RBFL_MAX_MODES];
+  if (t < RBFL_MAX_DET) sig_off[t] = c.sig_off[t];
+}
+
 }  // namespace rbfl

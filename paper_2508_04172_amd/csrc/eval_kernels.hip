@@ -239,18 +239,8 @@ __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restr
   const EvalConsts &c = *cp;
   const int64_t first = (int64_t)blockIdx.x * EB;
   const int cnt = (int)(nb - first < EB ? nb - first : EB);
-  // the harmonics' terms, word by word: n_modes of -m, then n_modes of +m
-  constexpr int kWords = sizeof(YlmTerms) / 4;
-  static_assert(sizeof(YlmTerms) % 4 == 0, "copied by words");
-  const int words = c.n_modes * kWords;
-  for (int e = threadIdx.x; e < 2 * words; e += kThreads)
-    reinterpret_cast<int *>(ylm)[e] =
-        e < words ? reinterpret_cast<const int *>(c.ylm_neg)[e] : reinterpret_cast<const int *>(c.ylm_pos)[e - words];
-  if (threadIdx.x < RBFL_MAX_DET * RBFL_MAX_MODES) {
-    const int e = threadIdx.x;
-    coef_off[e / RBFL_MAX_MODES][e % RBFL_MAX_MODES] = c.coef_off[e / RBFL_MAX_MODES][e % RBFL_MAX_MODES];
-    if (e < RBFL_MAX_DET) sig_off[e] = c.sig_off[e];
-  }
+  epi_copy_ylm(threadIdx.x, c, ylm);
+  epi_copy_offsets(threadIdx.x, c, coef_off, sig_off);
   __syncthreads();
   const int nm = c.n_modes;
   epi_setup_block([&](int) -> const EvalConsts & { return c; }, [&](int, int i) -> const YlmTerms & { return ylm[i]; },
@@ -262,6 +252,36 @@ __global__ void __launch_bounds__(kThreads) k_epilogue(const EvalConsts *__restr
     lnl[b0 + first + j] = v;
     if (nan) nan->part[first + j] = isnan(v) ? 1u : 0u;
   }
+}
+
+// The epilogue of a small batch whose setups the launch of the basis rows has
+// formed (k_rows_setup_fp64): a wave per proposal.  It is a chain of dependent
+// steps, and the setup, of trigonometry and powers, a good part of it (a whole
+// evaluation of 1021 proposals of 15 pairs: 62.2 to 59.3 us; of one pair and 512
+// proposals with 1504 rows: 36.5 to 34.6 us).
+__global__ void __launch_bounds__(kThreads) k_epilogue_ready(const EvalConsts *__restrict__ cp, int64_t b0, int64_t nb,
+                                                             const EpiSetup *__restrict__ setups,
+                                                             const double *__restrict__ Y,
+                                                             const double2 *__restrict__ basis4,
+                                                             double *__restrict__ lnl, NanCount *__restrict__ nan) {
+  __shared__ EpiSetup su[kWaves];
+  __shared__ int coef_off[RBFL_MAX_DET][RBFL_MAX_MODES], sig_off[RBFL_MAX_DET];
+  const EvalConsts &c = *cp;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * kWaves + wave;
+  epi_copy_offsets(threadIdx.x, c, coef_off, sig_off);
+  constexpr int kWords = sizeof(EpiSetup) / 8;
+  static_assert(sizeof(EpiSetup) % 8 == 0 && kWords <= 64, "copied by a wave at once");
+  if (j < nb && lane < kWords)
+    reinterpret_cast<double *>(&su[wave])[lane] = reinterpret_cast<const double *>(setups + j)[lane];
+  __syncthreads();
+  if (j >= nb) return;
+  const double v = epi_reduce<5>(c, su[wave], Y + j * c.Kp, basis4, coef_off, sig_off);
+  if (lane != 0) return;
+  lnl[b0 + j] = v;
+  if (!nan) return;
+  nan->part[j] = isnan(v) ? 1ull : 0ull;
+  if (j == 0) nan->slots = (unsigned long long)nb;
 }
 
 // Adds v to the compensated (Neumaier) sum (s, c).
@@ -795,6 +815,16 @@ bool launch_epilogue(const EvalConsts *c, const EvalConsts &hc, const double *pa
     else
       launch_epilogue_variant<16, kEpiUnroll>(c, params, ld, b0, nb, Y, basis, lnl, s, nan);
   }
+  RBFL_HIP(hipGetLastError());
+  return nan != nullptr;
+}
+
+// The same with the setups of the batch (at most kSetupMax proposals) at hand.
+bool launch_epilogue_ready(const EvalConsts *c, int64_t b0, int64_t nb, const void *setups, const double *Y,
+                           const double2 *basis, double *lnl, hipStream_t s, NanCount *nan) {
+  static_assert(kSetupMax <= kNanSlots, "one slot per proposal");
+  hipLaunchKernelGGL(k_epilogue_ready, dim3((unsigned)((nb + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, c, b0, nb,
+                     static_cast<const EpiSetup *>(setups), Y, basis, lnl, nan);
   RBFL_HIP(hipGetLastError());
   return nan != nullptr;
 }

@@ -128,16 +128,8 @@ __global__ void __launch_bounds__(512, 2)
                            __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
-    constexpr int kWords = sizeof(YlmTerms) / 4;
-    static_assert(sizeof(YlmTerms) % 4 == 0, "copied by words");
-    const int words = nm * kWords, e0 = t - 256;
-    for (int e = e0; e < 2 * words; e += 256)
-      reinterpret_cast<int *>(ylm)[e] = e < words ? reinterpret_cast<const int *>(c.ylm_neg)[e]
-                                                  : reinterpret_cast<const int *>(c.ylm_pos)[e - words];
-    if (e0 < RBFL_MAX_DET * RBFL_MAX_MODES) {
-      coef_off[e0 / RBFL_MAX_MODES][e0 % RBFL_MAX_MODES] = c.coef_off[e0 / RBFL_MAX_MODES][e0 % RBFL_MAX_MODES];
-      if (e0 < RBFL_MAX_DET) sig_off[e0] = c.sig_off[e0];
-    }
+    epi_copy_ylm(t - 256, c, ylm);
+    epi_copy_offsets(t - 256, c, coef_off, sig_off);
     __syncthreads();
     epi_setup_parts(t - 256, [&](int) -> const EvalConsts & { return c; },
                     [&](int, int i) -> const YlmTerms & { return ylm[i]; }, c.n_det, nm, params, ld, first, cnt, su,

@@ -28,6 +28,7 @@ void reserve(Ctx &c, int64_t n) {
   if (c.graph_users > 0) throw Error(RBFL_E_STATE, "the work space is captured by a sampler: it cannot grow");
   c.Y.alloc((size_t)n * c.Kp);
   c.Bt.alloc((size_t)c.rows * rows_ld(n));
+  c.small_su.alloc(epi_setup_bytes() * (size_t)std::min<int64_t>(n, kSetupMax));
   if (c.epi_su.p) reserve_lnl_gemm(c, n);
   c.cap = n;
   if (c.prepared[RBFL_FORM_BF16]) c.A16.alloc((size_t)c.rows * n);
@@ -42,8 +43,8 @@ void reserve(Ctx &c, int64_t n) {
   }
 }
 
-static void contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
-                     hipEvent_t *marks = nullptr);
+static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
+                     hipEvent_t *marks = nullptr, void *setups = nullptr);
 
 // True when `s` is being captured into a graph (or its capture state cannot
 // be read): the pipelined order forks onto a second stream, so such calls
@@ -221,6 +222,10 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
     eval_pipelined(c, params, ld, n, lnl, s);
     return false;
   }
+  auto finish = [&](int64_t b0, int64_t nb, bool ready) {
+    return ready ? launch_epilogue_ready(c.consts.p, b0, nb, c.small_su.p, c.Y.p, c.basis4.p, lnl, s, nan)
+                 : launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
+  };
   bool counted = false;
   for (int64_t b0 = 0; b0 < n; b0 += c.cap) {
     const int64_t nb = std::min(c.cap, n - b0);
@@ -232,16 +237,14 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
         RBFL_HIP(hipEventCreate(&e));
         c.timed_events.push_back(e);
       }
-      contract(c, params, ld, b0, nb, form, s, ev);
-      counted = launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
+      counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, ev, c.small_su.p));
       RBFL_HIP(hipEventRecord(ev[3], s));
       c.timed.push_back(Ctx::Timed{ev[0], ev[1], 2, nb});
       c.timed.push_back(Ctx::Timed{ev[1], ev[2], 0, nb});
       c.timed.push_back(Ctx::Timed{ev[2], ev[3], 1, nb});
       continue;
     }
-    contract(c, params, ld, b0, nb, form, s);
-    counted = launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
+    counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, nullptr, c.small_su.p));
   }
   return counted;
 }
@@ -256,17 +259,19 @@ void eval(Ctx &c, const double *params, int64_t n, double *lnl, int form, hipStr
 
 // The contraction of proposals [b0, b0 + nb) into the work space Y, in two
 // stages where the form has them (basis rows, then the MFMA product); marks,
-// when given, are recorded before, between and after the stages.
-static void contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
-                     hipEvent_t *marks) {
+// when given, are recorded before, between and after the stages.  Returns
+// whether the epilogue's setups have been formed too (into setups, when given).
+static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
+                     hipEvent_t *marks, void *setups) {
+  bool ready = false;
   auto mark = [&](int i) {
     if (marks) RBFL_HIP(hipEventRecord(marks[i], s));
   };
   auto fp64 = [&]() {
     const int v = c.variant[RBFL_FORM_FP64];
     if (v < gemm_fp64_variants()) {
-      launch_product_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Bt.p, c.Y.p, s, v,
-                          marks ? marks[1] : nullptr);
+      ready = launch_product_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Bt.p, c.Y.p, s, v,
+                                  marks ? marks[1] : nullptr, setups);
     } else {
       mark(1);
       launch_contract_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Y.p, s, 2);
@@ -304,6 +309,7 @@ static void contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64
                            marks ? marks[1] : nullptr);
   }
   mark(2);
+  return ready;
 }
 
 void interp(Ctx &c, const double *params, int64_t n, double *out, int form, hipStream_t s) {

@@ -223,6 +223,7 @@ struct Ctx {
   DevBuf<double2> win_D;       // exact outputs: brute_D with the window start's phase, made on first use
   DevBuf<int4> coldesc;        // output column layout (kind, detector, mode, index), [K]
   DevBuf<NanCount> nan;        // of the last evaluation call
+  DevBuf<unsigned char> small_su;   // epilogue setups of a small batch [min(cap, kSetupMax)]
   DevBuf<unsigned> small_done; // [kSmallBlocks / 2] finished workgroups of a one-launch evaluation, 0 between calls
   // reduced-precision weight copies
   DevBuf<float> W32;           // [rows][Kp]
@@ -364,11 +365,16 @@ double gemm_fp64_reuse(int variant);
 // The FP64 product Y of proposals b0 .. b0 + nb - 1 with tile `variant` (below
 // gemm_fp64_variants()): basis rows into Bt and their contraction, or in one
 // kernel where that is better; mid, when given, is recorded between the two.
-void launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+// setups, when given, holds min(nb, kSetupMax) epilogue setups; returns whether
+// they have been formed too (small batches).
+constexpr int kSetupMax = 4096;
+bool launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
-                         int variant, hipEvent_t mid);
-void launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant);
+                         int variant, hipEvent_t mid, void *setups = nullptr);
+bool launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups = nullptr);
+bool launch_epilogue_ready(const EvalConsts *c, int64_t b0, int64_t nb, const void *setups, const double *Y,
+                           const double2 *basis, double *lnl, hipStream_t s, NanCount *nan);
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
                       int variant);
 void launch_contract_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
