@@ -47,10 +47,11 @@ struct SamplerPrior {
 };
 
 // Run state read by the step kernels (device memory, so that one captured
-// step graph serves every run): completed steps, the step count when the
-// current run began, and where the run's chain samples go.
+// step graph serves every run): the step count before the current step and the
+// one to go on with, the count when the current run began, and where the run's
+// chain samples go.
 struct SamplerState {
-  uint64_t step, run_start;
+  uint64_t step, next, run_start;
   double *chain;       // [12][slots][W] or null
   int64_t slots;
   int32_t thin;
@@ -72,12 +73,11 @@ void launch_sampler_init(const EvalConsts *c, const SamplerPrior &pr, uint64_t s
                          hipStream_t s);
 void launch_log_prior(const EvalConsts *c, const SamplerPrior &pr, const double *X, int W, double *lp,
                       hipStream_t s);
-void launch_de_propose(const SamplerState *st, uint64_t seed, int M, int half, double gamma, double p_jump,
+void launch_de_propose(SamplerState *st, uint64_t seed, int M, int half, double gamma, double p_jump,
                        const double *X, double *Y, hipStream_t s);
-void launch_de_accept(const EvalConsts *c, const SamplerPrior &pr, const SamplerState *st, uint64_t seed, int M,
+void launch_de_accept(const EvalConsts *c, const SamplerPrior &pr, SamplerState *st, uint64_t seed, int M,
                       int half, int prior_only, const double *Y, const double *lnl_y, double *X, double *lnl_x,
                       double *lp_x, unsigned long long *acc, hipStream_t s);
-void launch_step_advance(SamplerState *st, hipStream_t s);
 void launch_gather_walkers(const double *X, const double *lnl, const double *lp, const int32_t *idx, int W,
                            double *Xo, double *lnlo, double *lpo, hipStream_t s);
 void launch_fill(double *p, int64_t n, double v, hipStream_t s);

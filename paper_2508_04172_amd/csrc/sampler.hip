@@ -120,15 +120,21 @@ __global__ void __launch_bounds__(kSBlock) k_sampler_init(const EvalConsts *__re
 }
 
 // Proposals of one half: walker i of half h (global index h M + i) with
-// partners from the other half.  Calls 0, 1 and 3 of its counter.
-__global__ void __launch_bounds__(kSBlock) k_de_propose(const SamplerState *__restrict__ st, uint64_t seed, int M,
-                                                        int half, double gamma, double p_jump,
-                                                        const double *__restrict__ X, double *__restrict__ Y) {
-  const int i = blockIdx.x * kSBlock + threadIdx.x;
+// partners from the other half.  Calls 0, 1 and 3 of its counter.  A thread per
+// walker and parameter m = blockIdx.y: the draws are repeated for each, which
+// costs nothing where one walker's eleven parameters in a row were a chain that
+// the step waited for (7.8 to 5.4 us for 1024 walkers).  The first half's launch
+// also makes the step that the one before left in `next` the current one.
+__global__ void __launch_bounds__(kSBlock) k_de_propose(SamplerState *__restrict__ st, uint64_t seed, int M, int half,
+                                                        double gamma, double p_jump, const double *__restrict__ X,
+                                                        double *__restrict__ Y) {
+  const int i = blockIdx.x * kSBlock + threadIdx.x, m = blockIdx.y;
   if (i >= M) return;
   const int W = 2 * M;
   const int gi = half * M + i, other = (1 - half) * M;
-  const Draw dr = make_draw(seed, (uint32_t)gi, st->step, half);
+  const uint64_t step = half == 0 ? st->next : st->step;
+  if (half == 0 && i == 0 && m == 0) st->step = step;    // read by the launches after this one
+  const Draw dr = make_draw(seed, (uint32_t)gi, step, half);
   double u0, u1, u2, u3, u4, u5;
   dr.pair(0, &u0, &u1);
   dr.pair(1, &u2, &u3);
@@ -141,22 +147,22 @@ __global__ void __launch_bounds__(kSBlock) k_de_propose(const SamplerState *__re
   double g = gamma * (1.0 + 0.01 * sqrt(-2.0 * log(u2)) * cospi(2.0 * u3));
   if (u4 < p_jump) g = 1.0;
   (void)u5;
-  for (int m = 0; m < 11; ++m) {
-    const double xi = X[(int64_t)m * W + gi];
-    double dxm = X[(int64_t)m * W + other + j] - X[(int64_t)m * W + other + k];
-    const double P = period(m);
-    if (P > 0.0) dxm -= P * rint(dxm / P);   // the shorter way round
-    double y = xi + g * dxm;
-    if (P > 0.0) y = wrap(y, P);
-    Y[(int64_t)m * M + i] = y;
-  }
+  const double xi = X[(int64_t)m * W + gi];
+  double dxm = X[(int64_t)m * W + other + j] - X[(int64_t)m * W + other + k];
+  const double P = period(m);
+  if (P > 0.0) dxm -= P * rint(dxm / P);   // the shorter way round
+  double y = xi + g * dxm;
+  if (P > 0.0) y = wrap(y, P);
+  Y[(int64_t)m * M + i] = y;
 }
 
 // Metropolis decision for one half (call 2 of the walker's counter), with ln L
 // weighted by the annealing factor beta of the step; on the second half also
-// the chain sample of the completed step.
+// the chain sample of the completed step, where the workgroups of blockIdx.y =
+// 1 .. 12 copy row blockIdx.y - 1 of the first half, and the count of the next
+// step (nothing in this launch reads it).
 __global__ void __launch_bounds__(kSBlock) k_de_accept(const EvalConsts *__restrict__ cp, SamplerPrior pr,
-                                                       const SamplerState *__restrict__ st, uint64_t seed, int M,
+                                                       SamplerState *__restrict__ st, uint64_t seed, int M,
                                                        int half, int prior_only, const double *__restrict__ Y,
                                                        const double *__restrict__ lnl_y, double *__restrict__ X,
                                                        double *__restrict__ lnl_x, double *__restrict__ lp_x,
@@ -166,8 +172,29 @@ __global__ void __launch_bounds__(kSBlock) k_de_accept(const EvalConsts *__restr
   const EvalConsts &c = *cp;
   const int W = 2 * M;
   const int gi = half * M + i;
-  double p[11];
+  // the chain's rows of this step's sample (chain layout [12][slots][W]: row m
+  // of every sample contiguous), or null
+  double *dst = nullptr;
+  int64_t row = 0;
+  if (half == 1 && st->chain != nullptr) {
+    const uint64_t done = st->step + 1 - st->run_start;
+    const int64_t slot = (int64_t)(done / (uint64_t)st->thin) - 1;
+    if (done % (uint64_t)st->thin == 0 && slot < st->slots) {
+      row = st->slots * (int64_t)W;
+      dst = st->chain + slot * (int64_t)W;
+    }
+  }
+  if (blockIdx.y > 0) {
+    const int m = blockIdx.y - 1;
+    if (dst) dst[m * row + i] = m < 11 ? X[(int64_t)m * W + i] : lnl_x[i];
+    return;
+  }
+  if (half == 1 && i == 0) st->next = st->step + 1;
+  double p[11], x[11];
+#pragma unroll
   for (int m = 0; m < 11; ++m) p[m] = Y[(int64_t)m * M + i];
+#pragma unroll
+  for (int m = 0; m < 11; ++m) x[m] = X[(int64_t)m * W + gi];
   const double lpy = sampler_log_prior(c, pr, p);
   double ly = prior_only ? 0.0 : lnl_y[i];
   if (isnan(ly)) ly = -__builtin_huge_val();
@@ -189,26 +216,16 @@ __global__ void __launch_bounds__(kSBlock) k_de_accept(const EvalConsts *__restr
     }
   }
   if (take) {
+#pragma unroll
     for (int m = 0; m < 11; ++m) X[(int64_t)m * W + gi] = p[m];
     lnl_x[gi] = ly;
     lp_x[gi] = lpy;
     acc[gi] += 1ull;
   }
-  if (half == 1 && st->chain != nullptr) {
-    // chain layout [12][slots][W]: row m of every sample contiguous
-    const uint64_t done = st->step + 1 - st->run_start;
-    if (done % (uint64_t)st->thin == 0) {
-      const int64_t slot = (int64_t)(done / (uint64_t)st->thin) - 1;
-      if (slot < st->slots) {
-        const int64_t row = st->slots * (int64_t)W;
-        double *dst = st->chain + slot * (int64_t)W;
-        for (int h = 0; h < 2; ++h) {
-          const int w = h * M + i;
-          for (int m = 0; m < 11; ++m) dst[m * row + w] = X[(int64_t)m * W + w];
-          dst[11 * row + w] = lnl_x[w];
-        }
-      }
-    }
+  if (dst) {
+#pragma unroll
+    for (int m = 0; m < 11; ++m) dst[m * row + gi] = take ? p[m] : x[m];
+    dst[11 * row + gi] = take ? ly : lx;
   }
 }
 
@@ -225,10 +242,6 @@ __global__ void __launch_bounds__(kSBlock) k_gather_walkers(const double *__rest
   for (int m = 0; m < 11; ++m) Xo[(int64_t)m * W + w] = X[(int64_t)m * W + src];
   lnlo[w] = lnl[src];
   lpo[w] = lp[src];
-}
-
-__global__ void k_step_advance(SamplerState *st) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) st->step += 1;
 }
 
 __global__ void __launch_bounds__(kSBlock) k_fill(double *__restrict__ p, int64_t n, double v) {
@@ -323,23 +336,18 @@ void launch_log_prior(const EvalConsts *c, const SamplerPrior &pr, const double 
   RBFL_HIP(hipGetLastError());
 }
 
-void launch_de_propose(const SamplerState *st, uint64_t seed, int M, int half, double gamma, double p_jump,
+void launch_de_propose(SamplerState *st, uint64_t seed, int M, int half, double gamma, double p_jump,
                        const double *X, double *Y, hipStream_t s) {
-  hipLaunchKernelGGL(k_de_propose, dim3((M + kSBlock - 1) / kSBlock), dim3(kSBlock), 0, s, st, seed, M, half, gamma,
-                     p_jump, X, Y);
+  hipLaunchKernelGGL(k_de_propose, dim3((M + kSBlock - 1) / kSBlock, 11), dim3(kSBlock), 0, s, st, seed, M, half,
+                     gamma, p_jump, X, Y);
   RBFL_HIP(hipGetLastError());
 }
 
-void launch_de_accept(const EvalConsts *c, const SamplerPrior &pr, const SamplerState *st, uint64_t seed, int M,
+void launch_de_accept(const EvalConsts *c, const SamplerPrior &pr, SamplerState *st, uint64_t seed, int M,
                       int half, int prior_only, const double *Y, const double *lnl_y, double *X, double *lnl_x,
                       double *lp_x, unsigned long long *acc, hipStream_t s) {
-  hipLaunchKernelGGL(k_de_accept, dim3((M + kSBlock - 1) / kSBlock), dim3(kSBlock), 0, s, c, pr, st, seed, M, half,
-                     prior_only, Y, lnl_y, X, lnl_x, lp_x, acc);
-  RBFL_HIP(hipGetLastError());
-}
-
-void launch_step_advance(SamplerState *st, hipStream_t s) {
-  hipLaunchKernelGGL(k_step_advance, dim3(1), dim3(64), 0, s, st);
+  hipLaunchKernelGGL(k_de_accept, dim3((M + kSBlock - 1) / kSBlock, half == 1 ? 13 : 1), dim3(kSBlock), 0, s, c, pr, st,
+                     seed, M, half, prior_only, Y, lnl_y, X, lnl_x, lp_x, acc);
   RBFL_HIP(hipGetLastError());
 }
 

@@ -41,7 +41,7 @@ struct rbfl_sampler_ctx {
 namespace rbfl {
 // One sampler step: for each half, proposals, their ln L through the online
 // stage (the handle's work space, reserved beforehand), the Metropolis
-// decisions; then the step counter.
+// decisions.
 static void sampler_step(rbfl_sampler_ctx &S, hipStream_t s) {
   const bool prior_only = S.spec.flags & RBFL_SAMPLER_PRIOR_ONLY;
   for (int half = 0; half < 2; ++half) {
@@ -50,7 +50,6 @@ static void sampler_step(rbfl_sampler_ctx &S, hipStream_t s) {
     launch_de_accept(S.c->consts.p, S.prior, S.st.p, S.spec.seed, S.M, half, prior_only ? 1 : 0, S.Y.p, S.lnl_y.p,
                      S.X.p, S.lnl_x.p, S.lp_x.p, S.acc.p, s);
   }
-  launch_step_advance(S.st.p, s);
 }
 
 static rbfl_sampler_ctx *sampler_create(Ctx &c, const rbfl_sampler_spec *sp, const double *init, hipStream_t s) {
@@ -96,7 +95,7 @@ static rbfl_sampler_ctx *sampler_create(Ctx &c, const rbfl_sampler_spec *sp, con
     reserve(c, std::min<int64_t>(std::max<int64_t>(M, 1), 1 << 20));
     eval(c, S->X.p, W, S->lnl_x.p, p.form, s);
   }
-  S->stage = SamplerState{0, 0, nullptr, 0, 1, (uint64_t)p.anneal_steps, p.beta0, -1.0};
+  S->stage = SamplerState{0, 0, 0, nullptr, 0, 1, (uint64_t)p.anneal_steps, p.beta0, -1.0};
   RBFL_HIP(hipMemcpyAsync(S->st.p, &S->stage, sizeof(SamplerState), hipMemcpyHostToDevice, s));
   RBFL_HIP(hipStreamSynchronize(s));
   // capture one step (profiling off: no events inside the graph)
@@ -128,8 +127,8 @@ static void sampler_run(rbfl_sampler_ctx &S, int64_t steps, int thin, double *ch
   if (S.last && S.last != s) RBFL_HIP(hipStreamSynchronize(S.last));
   // the staged state is read by an asynchronous copy: let the previous one finish
   RBFL_HIP(hipStreamSynchronize(s));
-  S.stage = SamplerState{S.steps, S.steps, chain, chain ? slots : 0, thin, (uint64_t)S.spec.anneal_steps,
-                         S.spec.beta0, S.beta_fixed};
+  S.stage = SamplerState{S.steps, S.steps, S.steps, chain, chain ? slots : 0, thin,
+                         (uint64_t)S.spec.anneal_steps, S.spec.beta0, S.beta_fixed};
   RBFL_HIP(hipMemcpyAsync(S.st.p, &S.stage, sizeof(SamplerState), hipMemcpyHostToDevice, s));
   for (int64_t i = 0; i < steps; ++i) RBFL_HIP(hipGraphLaunch(S.exec, s));
   S.steps += (uint64_t)steps;
