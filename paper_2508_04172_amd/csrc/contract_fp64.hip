@@ -84,7 +84,6 @@ __global__ void __launch_bounds__(256) k_rows_small_fp64(const EvalConsts *__res
 // k_rows_small_fp64 whose first n_setup workgroups form the setups of the
 // epilogue (kSetupGroup proposals each) instead: a chain of dependent steps that
 // the row values of the others hide.
-constexpr int kSetupGroup = 8;
 __global__ void __launch_bounds__(256) k_rows_setup_fp64(const EvalConsts *__restrict__ cp,
                                                          const double *__restrict__ params, int64_t ld, int64_t b0,
                                                          int nb, int ldb, int n_rows,
@@ -92,17 +91,8 @@ __global__ void __launch_bounds__(256) k_rows_setup_fp64(const EvalConsts *__res
                                                          int n_setup, EpiSetup *__restrict__ setups) {
   const EvalConsts &c = *cp;
   if ((int)blockIdx.x < n_setup) {
-    __shared__ EpiSetup su[kSetupGroup];
-    __shared__ EpiTmp tmp[kSetupGroup];
-    __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
-    const int first = blockIdx.x * kSetupGroup, cnt = min(kSetupGroup, nb - first);
-    epi_copy_ylm(threadIdx.x, c, ylm);
-    __syncthreads();
-    epi_setup_block([&](int) -> const EvalConsts & { return c; },
-                    [&](int, int i) -> const YlmTerms & { return ylm[i]; }, c.n_det, c.n_modes, params, ld, b0 + first,
-                    cnt, su, tmp);
-    for (int e = threadIdx.x; e < cnt * (int)(sizeof(EpiSetup) / 8); e += 256)
-      reinterpret_cast<double *>(setups + first)[e] = reinterpret_cast<const double *>(su)[e];
+    const int first = blockIdx.x * kSetupGroup;
+    epi_setups_out(c, params, ld, b0, first, min(kSetupGroup, nb - first), setups);
     return;
   }
   const unsigned t = (blockIdx.x - n_setup) * 256 + threadIdx.x;

@@ -130,6 +130,44 @@ __global__ void __launch_bounds__(256) k_split_rows(const EvalConsts *__restrict
   for (int i = 0; i < S; ++i) AS[((int64_t)i * G + g) * nb + q] = pack16(dg[i]);
 }
 
+// The same rows for small batches, four rows (a quarter of a group) per thread,
+// t = g4 nb + q, after n_setup workgroups that form the epilogue's setups: 16
+// exponentials and their digits in a row per thread are a chain that a launch of
+// few workgroups waits for.
+template <int S>
+__global__ void __launch_bounds__(256) k_split_rows_small(const EvalConsts *__restrict__ cp,
+                                                          const double *__restrict__ params, int64_t ld, int64_t b0,
+                                                          int nb, const double *__restrict__ nodes,
+                                                          int *__restrict__ AS, double *__restrict__ rscale,
+                                                          int n_setup, EpiSetup *__restrict__ setups) {
+  const EvalConsts &c = *cp;
+  if ((int)blockIdx.x < n_setup) {
+    const int first = blockIdx.x * kSetupGroup;
+    epi_setups_out(c, params, ld, b0, first, min(kSetupGroup, nb - first), setups);
+    return;
+  }
+  const unsigned t = (blockIdx.x - n_setup) * 256 + threadIdx.x;
+  const unsigned g4 = t / (unsigned)nb, q = t - g4 * (unsigned)nb;
+  if (g4 >= (unsigned)c.rows / 4) return;
+  double x[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) x[d] = params[d * ld + b0 + q] / c.semi[d];
+  const int N = c.N, NM = c.N + c.M, G = c.rows / 16;
+  const double sq = row_scale(x), inv = 1.0 / sq;    // powers of two: exact
+  if (g4 == 0) rscale[q] = sq;
+  int w[S] = {};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = 4 * (int)g4 + k;
+    int8_t a[S];
+    digits<S>(basis_row_fp64(r, N, NM, x, nodes + 4 * (int64_t)r, c.eps2, c.poly_idx) * inv, a);
+#pragma unroll
+    for (int i = 0; i < S; ++i) w[i] |= (int)(uint8_t)a[i] << (8 * k);
+  }
+#pragma unroll
+  for (int i = 0; i < S; ++i) AS[(((int64_t)i * G + (g4 >> 2)) * nb + q) * 4 + (g4 & 3)] = w[i];
+}
+
 // Power-of-two scale of each weight column: 2^e > max_r |W[r][c]|.
 __global__ void __launch_bounds__(256) k_col_scale(const double *__restrict__ W, int rows, int Kp,
                                                    double *__restrict__ scale) {
@@ -285,6 +323,85 @@ __global__ void __launch_bounds__(kSplitThreads, 1)
   split_tile<S>(AS, nb, rows, BS, cscale, rscale, Kp, Y, (tile / n_ct) * kSplitQ, (int)(tile % n_ct) * kSplitC);
 }
 
+// Small batches: 32 proposals x 32 columns per workgroup, a quarter of the rows
+// per wave, whose exact level sums meet in LDS: a 128 x 64 tile is one wave's
+// chain of all rows (34-42 us for 832 rows and 7 digits at any batch size), on 20
+// CUs for the first 128 proposals of 1280 columns.  Bound by the latency of the
+// loads, one step ahead of the MFMAs (11 us for as many tiles as there are CUs);
+// eight waves with an eighth of the rows each were slower (12 us; 32 against 28
+// for 512 proposals).  The sums are integers, so the outputs are those of
+// split_tile bit for bit.
+constexpr int kSplitTiny = 32;
+template <int S>
+__global__ void __launch_bounds__(kSplitThreads, 1)
+    k_split_small(const v4i *__restrict__ AS, int nb, int rows, const v4i *__restrict__ BS,
+                  const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp,
+                  double *__restrict__ Y) {
+  __shared__ int sums[S][16][64];
+  const int n_ct = Kp / kSplitTiny;
+  const int tile = (int)xcd_logical_block(blockIdx.x, gridDim.x);
+  const int q0 = tile / n_ct * kSplitTiny, c0 = tile % n_ct * kSplitTiny;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kh = lane >> 5, ml = lane & 31;
+  const int G = rows / 16, n_steps = rows / 32;
+  const int st0 = n_steps * wave / 4, st1 = n_steps * (wave + 1) / 4;
+  const int qa = min(q0 + ml, nb - 1);
+  const uint32_t oa = (uint32_t)((kh * nb + qa) * 16), ob = (uint32_t)((kh * Kp + c0 + ml) * 16);
+  const char *ca = reinterpret_cast<const char *>(AS), *cb = reinterpret_cast<const char *>(BS);
+  for (int e = threadIdx.x; e < S * 16 * 64; e += kSplitThreads) (&sums[0][0][0])[e] = 0;
+  __syncthreads();
+  v16i acc[S];
+#pragma unroll
+  for (int l = 0; l < S; ++l)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[l][r] = 0;
+  v4i a0[S], b0[S], a1[S], b1[S];      // two steps' operands, the next one's in flight
+  auto load = [&](int st, v4i *a, v4i *b) {
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      a[i] = *reinterpret_cast<const v4i *>(ca + ((int64_t)i * G + 2 * st) * nb * 16 + oa);
+      b[i] = *reinterpret_cast<const v4i *>(cb + ((int64_t)i * G + 2 * st) * Kp * 16 + ob);
+    }
+  };
+  auto multiply = [&](const v4i *a, const v4i *b) {
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = 0; i + j < S; ++j)
+        acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i + j], 0, 0, 0);
+  };
+  if (st0 < st1) {
+    load(st0, a0, b0);
+    int st = st0;
+    for (; st + 1 < st1; st += 2) {
+      load(st + 1, a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(a0, b0);
+      load(min(st + 2, st1 - 1), a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(a1, b1);
+    }
+    if (st < st1) multiply(a0, b0);
+#pragma unroll
+    for (int l = 0; l < S; ++l)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        __hip_atomic_fetch_add(&sums[l][r][lane], acc[l][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __syncthreads();
+  const int col = c0 + ml;
+  const double sc = cscale[col] * (1.0 / 16129.0);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int r = 4 * wave + k, q = q0 + 8 * (r >> 2) + 4 * kh + (r & 3);
+    if (q >= nb) continue;
+    double y = (double)sums[S - 1][r][lane];
+#pragma unroll
+    for (int l = S - 2; l >= 0; --l) y = fma(y, 1.0 / 254.0, (double)sums[l][r][lane]);
+    Y[(int64_t)q * Kp + col] = y * sc * rscale[q];
+  }
+}
+
 // The split contraction that finishes ln L itself (frozen antenna
 // patterns): the tile of split_accumulate, then each lane weights its 2 x 16
 // outputs (the values split_tile would store) by their columns' ln L weights
@@ -404,22 +521,50 @@ __global__ void k_zero_counters(unsigned long long *counter, int n) {
   if ((int)threadIdx.x < n) counter[threadIdx.x] = 0ull;
 }
 
+// Up to this many 32 x 32 output tiles (four rounds of the CUs, two workgroups on
+// each) k_split_small; more of them read their operands too often.  us for the
+// whole evaluation, small tiles / 128 x 64: 832 rows x 1280 columns 14 / 43 for one
+// proposal, 35 / 56 for 256 (320 tiles), 52 / 59 for 768 (960), 66 / 60 for 1021
+// (1280); x 256 columns 63 / 71 for 4096 (1024), 99 / 85 for 8192; 3008 x 2560 95 /
+// 131 for 256 (640), 155 / 137 for 512 (1280).
+constexpr int64_t kSplitSmallTiles = 1024;
+
 template <int S>
-void launch_variant(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+bool launch_variant(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                     int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
-                    const double *cscale, double *Y, hipStream_t s, hipEvent_t mid) {
+                    const double *cscale, double *Y, hipStream_t s, hipEvent_t mid, void *setups) {
   static_assert(S <= kMaxSlices && kColTile % kSplitC == 0 && kRowChunk % 32 == 0,
                 "K and the rows are padded to whole tiles");
   const int64_t G = hc.rows / 16;
-  hipLaunchKernelGGL((k_split_rows<S>), dim3((unsigned)((G * nb + 255) / 256)), dim3(256), 0, s, c, params, ld, b0,
-                     nb, nodes, reinterpret_cast<v4i *>(AS), rscale);
+  bool ready = false;
+  // as many row values as k_rows_small_fp64 takes (7.3 against 9.5 us for the rows
+  // of 16 proposals, 12.6 with the setups against 11.1 and 4 for 1021)
+  if (nb * hc.rows <= (1 << 20)) {
+    ready = setups != nullptr && nb <= kSetupMax && hc.n_bands <= 1;
+    const int n_setup = ready ? (int)((nb + kSetupGroup - 1) / kSetupGroup) : 0;
+    hipLaunchKernelGGL((k_split_rows_small<S>), dim3(n_setup + (unsigned)((4 * G * nb + 255) / 256)), dim3(256), 0, s, c,
+                       params, ld, b0, (int)nb, nodes, reinterpret_cast<int *>(AS), rscale, n_setup,
+                       static_cast<EpiSetup *>(setups));
+  } else {
+    hipLaunchKernelGGL((k_split_rows<S>), dim3((unsigned)((G * nb + 255) / 256)), dim3(256), 0, s, c, params, ld, b0,
+                       nb, nodes, reinterpret_cast<v4i *>(AS), rscale);
+  }
   RBFL_HIP(hipGetLastError());
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
+  const int64_t tiny = (nb + kSplitTiny - 1) / kSplitTiny * (hc.Kp / kSplitTiny);
+  if (tiny <= kSplitSmallTiles) {
+    hipLaunchKernelGGL((k_split_small<S>), dim3((unsigned)tiny), dim3(kSplitThreads), 0, s,
+                       reinterpret_cast<const v4i *>(AS), (int)nb, hc.rows, reinterpret_cast<const v4i *>(BS), cscale,
+                       rscale, hc.Kp, Y);
+    RBFL_HIP(hipGetLastError());
+    return ready;
+  }
   const int64_t nblk = (nb + kSplitQ - 1) / kSplitQ * (hc.Kp / kSplitC);
   hipLaunchKernelGGL((k_split_contract<S>), dim3((unsigned)nblk), dim3(kSplitThreads), 0, s,
                      reinterpret_cast<const v4i *>(AS), nb, hc.rows, reinterpret_cast<const v4i *>(BS), cscale,
                      rscale, hc.Kp, Y);
   RBFL_HIP(hipGetLastError());
+  return ready;
 }
 
 template <int S>
@@ -507,16 +652,17 @@ void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *p
   }
 }
 
-void launch_contract_split(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+bool launch_contract_split(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                            int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
-                           const double *cscale, double *Y, hipStream_t s, int variant, hipEvent_t mid) {
+                           const double *cscale, double *Y, hipStream_t s, int variant, hipEvent_t mid,
+                           void *setups) {
   if (hc.rows > kMaxSplitRows || hc.rows % 32 != 0 || hc.Kp % kSplitC != 0)
     throw Error(RBFL_E_UNSUPPORTED, "split form: rows must be a multiple of 32 and at most 16384");
   switch (variant) {
-    case 0: launch_variant<5>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid); break;
-    case 1: launch_variant<6>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid); break;
-    case 2: launch_variant<7>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid); break;
-    case 3: launch_variant<8>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid); break;
+    case 0: return launch_variant<5>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid, setups);
+    case 1: return launch_variant<6>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid, setups);
+    case 2: return launch_variant<7>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid, setups);
+    case 3: return launch_variant<8>(c, hc, params, ld, b0, nb, nodes, AS, rscale, BS, cscale, Y, s, mid, setups);
     default: throw Error(RBFL_E_INVALID_ARG, "unknown split-form variant");
   }
 }

@@ -341,6 +341,22 @@ __device__ __forceinline__ void epi_copy_ylm(int t, const EvalConsts &c, YlmTerm
         e < words ? reinterpret_cast<const int *>(c.ylm_neg)[e] : reinterpret_cast<const int *>(c.ylm_pos)[e - words];
 }
 
+// Setups first .. first + cnt - 1 of a batch (cnt <= kSetupGroup) to memory, by a
+// workgroup of 256 threads of the launch that forms the basis rows.
+constexpr int kSetupGroup = 8;
+__device__ __forceinline__ void epi_setups_out(const EvalConsts &c, const double *__restrict__ params, int64_t ld,
+                                               int64_t b0, int first, int cnt, EpiSetup *__restrict__ setups) {
+  __shared__ EpiSetup su[kSetupGroup];
+  __shared__ EpiTmp tmp[kSetupGroup];
+  __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
+  epi_copy_ylm(threadIdx.x, c, ylm);
+  __syncthreads();
+  epi_setup_block([&](int) -> const EvalConsts & { return c; }, [&](int, int i) -> const YlmTerms & { return ylm[i]; },
+                  c.n_det, c.n_modes, params, ld, b0 + first, cnt, su, tmp);
+  for (int e = threadIdx.x; e < cnt * (int)(sizeof(EpiSetup) / 8); e += 256)
+    reinterpret_cast<double *>(setups + first)[e] = reinterpret_cast<const double *>(su)[e];
+}
+
 // c's output offsets likewise.
 __device__ __forceinline__ void epi_copy_offsets(int t, const EvalConsts &c, int (*coef_off)[RBFL_MAX_MODES],
                                                  int *sig_off) {

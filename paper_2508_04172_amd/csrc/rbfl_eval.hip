@@ -288,8 +288,8 @@ static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64
                            c.variant[form]);
       break;
     case RBFL_FORM_SPLIT:
-      launch_contract_split(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.AS.p, c.ASscale.p, c.WS.p,
-                            c.WSscale.p, c.Y.p, s, c.variant[form], marks ? marks[1] : nullptr);
+      ready = launch_contract_split(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.AS.p, c.ASscale.p,
+                                    c.WS.p, c.WSscale.p, c.Y.p, s, c.variant[form], marks ? marks[1] : nullptr, setups);
       break;
     case RBFL_FORM_SURROGATE:
       if (c.sur && c.sur_ok) {

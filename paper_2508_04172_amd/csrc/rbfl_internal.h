@@ -436,9 +436,11 @@ int split_variant_slices(int variant);
 const char *split_variant_name(int variant);
 constexpr int kSplitDefaultVariant = 2;    // 7 base-254 digits: within a few units of FP64 rounding
 void launch_split_prepare(const double *W, int rows, int Kp, double *scale, int8_t *BS, hipStream_t s);
-void launch_contract_split(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
+// setups as for launch_product_fp64.
+bool launch_contract_split(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                            int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
-                           const double *scale, double *Y, hipStream_t s, int variant, hipEvent_t mid);
+                           const double *scale, double *Y, hipStream_t s, int variant, hipEvent_t mid,
+                           void *setups = nullptr);
 // The split form with ln L finished inside its contraction (frozen patterns):
 // digit rows, then one partial sum per proposal and split_col_tile()-column
 // tile into part[tile][ldp] from the setups of launch_epi_setup; mid, when

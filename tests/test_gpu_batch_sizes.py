@@ -167,3 +167,34 @@ def test_one_launch(sites, modes, nodes, degree, q, sizes):
         for _ in range(2):                            # the second finds the counters that the first left
             assert np.array_equal(lnl(h, sub), want, equal_nan=True)
             assert h.nan_count() == int(np.isnan(want).sum())
+
+
+# split form, 256 columns: 32 x 32 tiles up to 1024 of them (4096 proposals), four
+# rows per thread up to 2^20 row values (10,922 proposals of 96 rows)
+@pytest.mark.parametrize("v, sizes", [(2, [1, 31, 32, 33, 1021, 4096, 4097, 10_922, 10_923]), (0, [1, 100]),
+                                      (1, [33, 700]), (3, [17, 4096])])
+def test_split_batch_size(case, v, sizes):
+    import torch
+    h, p, _, _ = case
+    stream = torch.cuda.current_stream().cuda_stream
+    n_all = 20_000
+
+    def run(sub):
+        n = sub.shape[1]
+        out = torch.empty(n, h.sizes()["K"], device="cuda", dtype=torch.float64)
+        l = torch.empty(n, device="cuda", dtype=torch.float64)
+        h.interp(sub.data_ptr(), n, out.data_ptr(), rbfl.FORM_SPLIT, stream)
+        h.eval(sub.data_ptr(), n, l.data_ptr(), rbfl.FORM_SPLIT, stream)
+        return out, l.cpu().numpy()
+
+    h.prepare(rbfl.FORM_SPLIT)
+    h.set_variant(rbfl.FORM_SPLIT, v)
+    ref, ref_lnl = run(p[:, :n_all].contiguous())
+    for n in sizes:
+        got, got_lnl = run(p[:, n_all - n:n_all].contiguous())
+        # integer sums, combined alike: the outputs agree bit for bit; ln L as in test_batch_size
+        assert torch.equal(got, ref[n_all - n:])
+        want = ref_lnl[n_all - n:]
+        fin = np.isfinite(want)
+        assert np.array_equal(fin, np.isfinite(got_lnl))
+        assert fin.sum() == 0 or np.abs(got_lnl[fin] - want[fin]).max() <= 1e-8
