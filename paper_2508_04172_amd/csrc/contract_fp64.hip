@@ -218,8 +218,7 @@ __device__ __forceinline__ void gemm_tile(const double *__restrict__ Bt, int64_t
 template <int RT, int CT, int KC, int WQ, int WC>
 __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
     k_gemm_fp64(const double *__restrict__ Bt, int64_t nb, int64_t ldb, int rows, const double *__restrict__ W,
-                int Kp, double *__restrict__ Y) {
-  const int n_ct = Kp / (WC * CT * 16);
+                int Kp, int n_ct, double *__restrict__ Y) {
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
   gemm_tile<RT, CT, KC, WQ, WC>(Bt, nb, ldb, rows, W, Kp, Y, tile / n_ct, (int)(tile % n_ct));
 }
@@ -228,7 +227,7 @@ constexpr int kFormRowsQ = 64;   // proposals per workgroup of k_rows_gemm_fp64
 
 // Contraction that forms its own rows, for handles whose columns fit one tile
 // (Kp = 128): 64 proposals x all columns per workgroup of 2 x 2 waves, each
-// 2 x 4 tiles of 16 x 16, chunks of KC rows.  With one column tile every row
+// 2 x CT tiles of 16 x 16 (CT = the K / 32 rounded up), chunks of KC rows.  With one column tile every row
 // value is used by one workgroup only, so writing it to HBM and reading it back
 // buys nothing: each wave forms its share of the next chunk's rows (a lane per
 // proposal, the nodes in scalar registers) straight into LDS before it
@@ -237,14 +236,16 @@ constexpr int kFormRowsQ = 64;   // proposals per workgroup of k_rows_gemm_fp64
 // workgroup against 2048 of MFMA alone); the rows' round trip costs more
 // (1536 rows, 5e5 proposals: 3.68 ms against 1.22 ms of rows and 3.46 ms of
 // product).  With 256 columns and 8 waves it does not (4.25 against 4.10 ms).
-// Same row values, same MFMA order: the outputs are those of k_gemm_fp64 bit
-// for bit.
-template <int KC>
+// With fewer columns only the tiles that
+// hold them (41 columns, 208 rows, 3e5 proposals: 483 to 354 us for the whole
+// evaluation).  Same row values, same MFMA order: the outputs are those of
+// k_gemm_fp64 bit for bit.
+template <int KC, int CT>
 __global__ void __launch_bounds__(256)
     k_rows_gemm_fp64(const EvalConsts *__restrict__ cp, const double *__restrict__ params, int64_t ld, int64_t b0,
                      int64_t nb, const double *__restrict__ nodes, int rows, const double *__restrict__ W,
                      double *__restrict__ Y) {
-  constexpr int RT = 2, CT = 4, WQ = 2, QT = kFormRowsQ, CW = 128, NT = 256, NW = 4;
+  constexpr int RT = 2, WQ = 2, QT = kFormRowsQ, CW = 32 * CT, LD = 128, NT = 256, NW = 4;
   constexpr int LW = KC * CW / 2 / NT;     // double2 entries of W per thread and chunk
   constexpr int PR = KC / NW;              // rows of a chunk that a wave forms
   static_assert(KC * CW / 2 % NT == 0 && KC % NW == 0 && KC % 4 == 0, "even shares");
@@ -278,12 +279,12 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
   for (int u = 0; u < LW; ++u) {
     const int e = tid + u * NT;
-    pw[u] = W + (int64_t)(e / (CW / 2)) * CW + 2 * (e % (CW / 2));
+    pw[u] = W + (int64_t)(e / (CW / 2)) * LD + 2 * (e % (CW / 2));
   }
   d2 rw[LW];
   auto fetch = [&](int ch) {
 #pragma unroll
-    for (int u = 0; u < LW; ++u) rw[u] = *reinterpret_cast<const d2 *>(pw[u] + (int64_t)ch * KC * CW);
+    for (int u = 0; u < LW; ++u) rw[u] = *reinterpret_cast<const d2 *>(pw[u] + (int64_t)ch * KC * LD);
   };
   auto stash = [&](int buf) {
     asm volatile("" ::: "memory");
@@ -332,7 +333,7 @@ __global__ void __launch_bounds__(256)
       const int64_t q = q0 + wq * RT * 16 + 16 * t + kk + 4 * i;
       if (q >= nb) continue;
 #pragma unroll
-      for (int u = 0; u < CT; ++u) Y[q * CW + wc * CT * 16 + 16 * u + ll] = acc[t][u][i];
+      for (int u = 0; u < CT; ++u) Y[q * LD + wc * CT * 16 + 16 * u + ll] = acc[t][u][i];
     }
 }
 
@@ -663,8 +664,7 @@ __device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, i
 
 __global__ void __launch_bounds__(256)
     k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int64_t ldb, int rows, const double *__restrict__ W,
-                      int Kp, double *__restrict__ Y) {
-  const int n_ct = Kp / kTinyTile;
+                      int Kp, int n_ct, double *__restrict__ Y) {
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
   gemm_small_tile(Bt, nb, ldb, rows, W, Kp, Y, (int)(tile / n_ct) * kTinyTile, (int)(tile % n_ct) * kTinyTile);
 }
@@ -690,18 +690,20 @@ void launch_gemm(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc
                  hipStream_t s) {
   constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
   static_assert(kColTile % CW == 0 && kRowChunk % KC == 0 && 16 % KC == 0, "K and the rows are padded to whole tiles");
-  const int64_t nblk = (nb + QT - 1) / QT * (hc.Kp / CW);
+  const int n_ct = col_tiles(hc, CW);
+  const int64_t nblk = (nb + QT - 1) / QT * n_ct;
   hipLaunchKernelGGL((k_gemm_fp64<RT, CT, KC, WQ, WC>), dim3((unsigned)nblk), dim3(64 * WQ * WC), 0, s, Bt, nb, ldb,
-                     gemm_rows(hc, KC), W, hc.Kp, Y);
+                     gemm_rows(hc, KC), W, hc.Kp, n_ct, Y);
   RBFL_HIP(hipGetLastError());
 }
 
 void launch_gemm_small(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc, const double *W, double *Y,
                        hipStream_t s) {
   static_assert(kColTile % kTinyTile == 0 && kRowChunk % (2 * kTinyKC) == 0, "whole tiles and chunk pairs");
-  const int64_t nblk = (nb + kTinyTile - 1) / kTinyTile * (hc.Kp / kTinyTile);
+  const int n_ct = col_tiles(hc, kTinyTile);
+  const int64_t nblk = (nb + kTinyTile - 1) / kTinyTile * n_ct;
   hipLaunchKernelGGL(k_gemm_small_fp64, dim3((unsigned)nblk), dim3(256), 0, s, Bt, (int)nb, ldb,
-                     gemm_rows(hc, 2 * kTinyKC), W, hc.Kp, Y);
+                     gemm_rows(hc, 2 * kTinyKC), W, hc.Kp, n_ct, Y);
   RBFL_HIP(hipGetLastError());
 }
 
@@ -720,7 +722,7 @@ void launch_gemm_small(const double *Bt, int64_t nb, int64_t ldb, const EvalCons
 // 1500 (3760), 1138 / 982 / 1152 at 4000, 2343 / 1922 / 1921 at 8192 (20480).
 // All give the same bits.
 constexpr int64_t kTinyTiles = 2880, kMidTiles = 22000;
-static int64_t tiles32(const EvalConsts &hc, int64_t nb) { return (nb + 31) / 32 * (hc.Kp / 32); }
+static int64_t tiles32(const EvalConsts &hc, int64_t nb) { return (nb + 31) / 32 * col_tiles(hc, 32); }
 
 // How many of a batch's first proposals the variant's tile takes; the rest goes
 // to the smaller ones.  None below kMidTiles.  The 8-wave tiles (256 x 128, one
@@ -804,8 +806,16 @@ int64_t gemm_own_rows(const EvalConsts &hc, int64_t nb) {
 void launch_rows_gemm_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                            int64_t nb, const double *nodes, const double *W, double *Y, hipStream_t s) {
   constexpr int KC = 16;
-  hipLaunchKernelGGL(k_rows_gemm_fp64<KC>, dim3((unsigned)((nb + kFormRowsQ - 1) / kFormRowsQ)), dim3(256), 0, s, c,
-                     params, ld, b0, nb, nodes, gemm_rows(hc, KC), W, Y);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((nb + kFormRowsQ - 1) / kFormRowsQ)), dim3(256), 0, s, c, params, ld, b0,
+                       nb, nodes, gemm_rows(hc, KC), W, Y);
+  };
+  switch (col_tiles(hc, 32)) {
+    case 1: launch(k_rows_gemm_fp64<KC, 1>); break;
+    case 2: launch(k_rows_gemm_fp64<KC, 2>); break;
+    case 3: launch(k_rows_gemm_fp64<KC, 3>); break;
+    default: launch(k_rows_gemm_fp64<KC, 4>);
+  }
   RBFL_HIP(hipGetLastError());
 }
 

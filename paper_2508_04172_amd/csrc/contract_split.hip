@@ -316,9 +316,8 @@ __device__ __forceinline__ void split_tile(const v4i *__restrict__ AS, int64_t n
 template <int S>
 __global__ void __launch_bounds__(kSplitThreads, 1)
     k_split_contract(const v4i *__restrict__ AS, int64_t nb, int rows, const v4i *__restrict__ BS,
-                     const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp,
+                     const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp, int n_ct,
                      double *__restrict__ Y) {
-  const int n_ct = Kp / kSplitC;
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
   split_tile<S>(AS, nb, rows, BS, cscale, rscale, Kp, Y, (tile / n_ct) * kSplitQ, (int)(tile % n_ct) * kSplitC);
 }
@@ -335,10 +334,9 @@ constexpr int kSplitTiny = 32;
 template <int S>
 __global__ void __launch_bounds__(kSplitThreads, 1)
     k_split_small(const v4i *__restrict__ AS, int nb, int rows, const v4i *__restrict__ BS,
-                  const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp,
+                  const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp, int n_ct,
                   double *__restrict__ Y) {
   __shared__ int sums[S][16][64];
-  const int n_ct = Kp / kSplitTiny;
   const int tile = (int)xcd_logical_block(blockIdx.x, gridDim.x);
   const int q0 = tile / n_ct * kSplitTiny, c0 = tile % n_ct * kSplitTiny;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -412,11 +410,10 @@ __global__ void __launch_bounds__(kSplitThreads, 1)
 template <int S>
 __global__ void __launch_bounds__(kSplitThreads, 1)
     k_split_lnl(const v4i *__restrict__ AS, int64_t nb, int rows, const v4i *__restrict__ BS,
-                const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp,
+                const double *__restrict__ cscale, const double *__restrict__ rscale, int Kp, int n_ct,
                 const EvalConsts *__restrict__ cp, const EpiSetup *__restrict__ setups,
                 const double2 *__restrict__ basis4, const int4 *__restrict__ coldesc, double *__restrict__ part,
                 int64_t ldp) {
-  const int n_ct = Kp / kSplitC;
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
   const int64_t q0 = (tile / n_ct) * kSplitQ;
   const int tc = (int)(tile % n_ct), c0 = tc * kSplitC;
@@ -551,18 +548,19 @@ bool launch_variant(const EvalConsts *c, const EvalConsts &hc, const double *par
   }
   RBFL_HIP(hipGetLastError());
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
-  const int64_t tiny = (nb + kSplitTiny - 1) / kSplitTiny * (hc.Kp / kSplitTiny);
+  const int n_tiny = col_tiles(hc, kSplitTiny), n_ct = col_tiles(hc, kSplitC);
+  const int64_t tiny = (nb + kSplitTiny - 1) / kSplitTiny * n_tiny;
   if (tiny <= kSplitSmallTiles) {
     hipLaunchKernelGGL((k_split_small<S>), dim3((unsigned)tiny), dim3(kSplitThreads), 0, s,
                        reinterpret_cast<const v4i *>(AS), (int)nb, hc.rows, reinterpret_cast<const v4i *>(BS), cscale,
-                       rscale, hc.Kp, Y);
+                       rscale, hc.Kp, n_tiny, Y);
     RBFL_HIP(hipGetLastError());
     return ready;
   }
-  const int64_t nblk = (nb + kSplitQ - 1) / kSplitQ * (hc.Kp / kSplitC);
+  const int64_t nblk = (nb + kSplitQ - 1) / kSplitQ * n_ct;
   hipLaunchKernelGGL((k_split_contract<S>), dim3((unsigned)nblk), dim3(kSplitThreads), 0, s,
                      reinterpret_cast<const v4i *>(AS), nb, hc.rows, reinterpret_cast<const v4i *>(BS), cscale,
-                     rscale, hc.Kp, Y);
+                     rscale, hc.Kp, n_ct, Y);
   RBFL_HIP(hipGetLastError());
   return ready;
 }
@@ -577,10 +575,11 @@ void launch_lnl_variant(const EvalConsts *c, const EvalConsts &hc, const double 
                      nb, nodes, reinterpret_cast<v4i *>(AS), rscale);
   RBFL_HIP(hipGetLastError());
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
-  const int64_t nblk = (nb + kSplitQ - 1) / kSplitQ * (hc.Kp / kSplitC);
+  const int n_ct = col_tiles(hc, kSplitC);
+  const int64_t nblk = (nb + kSplitQ - 1) / kSplitQ * n_ct;
   hipLaunchKernelGGL((k_split_lnl<S>), dim3((unsigned)nblk), dim3(kSplitThreads), 0, s,
                      reinterpret_cast<const v4i *>(AS), nb, hc.rows, reinterpret_cast<const v4i *>(BS), cscale,
-                     rscale, hc.Kp, c, static_cast<const EpiSetup *>(setups), basis4, coldesc, part, ldp);
+                     rscale, hc.Kp, n_ct, c, static_cast<const EpiSetup *>(setups), basis4, coldesc, part, ldp);
   RBFL_HIP(hipGetLastError());
 }
 

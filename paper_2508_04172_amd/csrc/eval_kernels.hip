@@ -685,7 +685,7 @@ static void launch_fp64_variant(const EvalConsts *c, const EvalConsts &hc, const
   static_assert(kColTile % (CT * 16) == 0, "K is padded to a multiple of every column tile");
   const int64_t qt = kWaves * RT * 16;
   const int cw = CT * 16;
-  dim3 grid((unsigned)((nb + qt - 1) / qt), (unsigned)((hc.Kp + cw - 1) / cw));
+  dim3 grid((unsigned)((nb + qt - 1) / qt), (unsigned)col_tiles(hc, cw));
   hipLaunchKernelGGL((k_contract_fp64<RT, CT, CH>), grid, dim3(kThreads), 0, s, c, params, ld, b0, nb, nodes, W, Y);
   RBFL_HIP(hipGetLastError());
 }
@@ -721,7 +721,7 @@ static void launch_fp32_variant(const EvalConsts *c, const EvalConsts &hc, const
   static_assert(kColTile % (CT * 16) == 0 && kRowChunk % CH == 0, "K and the rows are padded to whole tiles");
   const int64_t qt = kWaves * RT * 16;
   const int cw = CT * 16;
-  dim3 grid((unsigned)((nb + qt - 1) / qt), (unsigned)((hc.Kp + cw - 1) / cw));
+  dim3 grid((unsigned)((nb + qt - 1) / qt), (unsigned)col_tiles(hc, cw));
   hipLaunchKernelGGL((k_contract_fp32<RT, CT, CH>), grid, dim3(kThreads), 0, s, c, params, ld, b0, nb, nodes, W, Y);
   RBFL_HIP(hipGetLastError());
 }

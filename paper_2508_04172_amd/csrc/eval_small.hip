@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(512, 2)
 // for 1024 (1792); at 1504 x 128 33.8 / 25.6 for 256 (3008); at 3008 x 2560 57 /
 // 49 for 6 (3008).
 int small_eval_group(const EvalConsts &hc, int64_t n) {
-  const int n_ct = hc.Kp / 64;
+  const int n_ct = col_tiles(hc, 64);
   if (hc.n_bands > 1 || n > (int64_t)kMaxGroup * (kSmallBlocks / n_ct)) return 0;
   for (int slots = 1; slots <= kMaxGroup && slots * hc.rows <= kMaxRowValues; slots *= 2)
     if ((n + slots - 1) / slots * n_ct <= kSmallBlocks) return slots;
@@ -174,7 +174,7 @@ void launch_eval_small(int slots, const EvalConsts *c, const EvalConsts &hc, con
                        int64_t n, const double *nodes, const double *W, double *Y, const double2 *basis4, double *lnl,
                        NanCount *nan, unsigned *done, hipStream_t s) {
   const unsigned groups = (unsigned)((n + slots - 1) / slots);
-  hipLaunchKernelGGL(k_eval_small, dim3(hc.Kp / 64, groups), dim3(512), shared_bytes(hc, slots), s, c, params, ld,
+  hipLaunchKernelGGL(k_eval_small, dim3(col_tiles(hc, 64), groups), dim3(512), shared_bytes(hc, slots), s, c, params, ld,
                      (int)n, slots, nodes, W, Y, basis4, lnl, nan, done);
   RBFL_HIP(hipGetLastError());
 }

@@ -162,7 +162,7 @@ static void eval_lnl_gemm(Ctx &c, const double *params, int64_t ld, int64_t n, d
 
 // The split form with ln L finished inside its contraction, chunk by chunk.
 static void eval_split_lnl(Ctx &c, const double *params, int64_t ld, int64_t n, double *lnl, hipStream_t s) {
-  const int n_ct = c.Kp / split_col_tile();
+  const int n_ct = col_tiles(c.host_consts, split_col_tile());
   if (!c.epi_su.p) {
     if (capturing(s)) throw Error(RBFL_E_STATE, "work space of the fused epilogue not allocated (evaluate once before capture)");
     reserve_lnl_gemm(c, c.cap);

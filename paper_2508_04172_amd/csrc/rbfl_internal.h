@@ -224,7 +224,7 @@ struct Ctx {
   DevBuf<int4> coldesc;        // output column layout (kind, detector, mode, index), [K]
   DevBuf<NanCount> nan;        // of the last evaluation call
   DevBuf<unsigned char> small_su;   // epilogue setups of a small batch [min(cap, kSetupMax)]
-  DevBuf<unsigned> small_done; // [kSmallBlocks / 2] finished workgroups of a one-launch evaluation, 0 between calls
+  DevBuf<unsigned> small_done; // [kSmallBlocks] finished workgroups of a one-launch evaluation, 0 between calls
   // reduced-precision weight copies
   DevBuf<float> W32;           // [rows][Kp]
   DevBuf<uint16_t> W16;        // BF16 form: weights in 8-row groups [rows/8][Kp][8]
@@ -357,6 +357,9 @@ void launch_transpose_weights(const double *R, int NM, int K, int rows, int Kp, 
 // ---- online kernels (eval_kernels.hip) ----
 int contract_variants(int form);
 const char *contract_variant_name(int form, int variant);
+// Column tiles of a contraction: those of padding columns alone are left out
+// (nothing reads Y past column K).
+inline int col_tiles(const EvalConsts &hc, int width) { return (hc.K + width - 1) / width; }
 // ---- FP64 rows + GEMM (contract_fp64.hip) ----
 int64_t rows_ld(int64_t n);
 int gemm_fp64_variants();
@@ -451,8 +454,8 @@ void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *p
                       const double *cscale, const void *setups, const double2 *basis4, const int4 *coldesc,
                       double *part, int64_t ldp, hipStream_t s, int variant, hipEvent_t mid);
 // FP64 ln L of n proposals in one launch (eval_small.hip), `slots` =
-// small_eval_group(n) of them per workgroup (0: n is too large); done[kSmallBlocks
-// / 2] holds zeros between the launches, nan is filled too.
+// small_eval_group(n) of them per workgroup (0: n is too large); done[kSmallBlocks]
+// holds zeros between the launches, nan is filled too.
 constexpr int kSmallBlocks = 256;
 int small_eval_group(const EvalConsts &hc, int64_t n);
 void launch_eval_small(int slots, const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,

@@ -121,7 +121,7 @@ static void plan_layout(Plan &p, int v, hipStream_t s) {
   p.small = 0;
   if (v >= ragged_fused_variants()) {
     int64_t tiles = 0;
-    for (int e = 0; e < n_ev; ++e) tiles += (p.counts[e] + 31) / 32 * (p.ctx[e]->Kp / 32);
+    for (int e = 0; e < n_ev; ++e) tiles += (p.counts[e] + 31) / 32 * col_tiles(p.ctx[e]->host_consts, 32);
     p.small = ragged_small_tile(tiles);
     if (p.small) qt = cw = 32 * p.small;
   }
@@ -142,7 +142,7 @@ static void plan_layout(Plan &p, int v, hipStream_t s) {
     d[e].ldb = rows_ld(p.counts[e]);
     d[e].rg0 = rg;
     d[e].tiles_q = (int)((p.counts[e] + qt - 1) / qt);
-    d[e].tiles_c = c.Kp / cw;
+    d[e].tiles_c = col_tiles(c.host_consts, cw);
     d[e].Kp = c.Kp;
     d[e].rows = c.rows;
     q0 += p.counts[e];
@@ -195,7 +195,7 @@ static void plan_layout_split(Plan &p, hipStream_t s) {
     x.q0 = q0;
     x.n = p.counts[e];
     x.tiles_q = (int)((p.counts[e] + qt - 1) / qt);
-    x.tiles_c = c.Kp / cw;
+    x.tiles_c = col_tiles(c.host_consts, cw);
     x.Kp = c.Kp;
     x.rows = c.rows;
     x.BS = c.WS.p;

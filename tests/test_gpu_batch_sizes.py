@@ -87,9 +87,9 @@ def test_large_tiles_agree(case, v, n):
         h.set_variant(rbfl.FORM_FP64, 0)
 
 
-# two events of 256 and 128 padded columns: 8 and 4 tiles of 32 per 32 proposals,
-# so the plan's tiles change at 2880 and 22000 of them
-@pytest.mark.parametrize("counts", [(1, 1), (33, 700), (11_489, 1), (8000, 8191), (60_000, 9000), (60_001, 60_000)])
+# two events of 243 and 19 columns: 8 and 1 tiles of 32 per 32 proposals, so the
+# plan's tiles change at 2880 and 22000 of them
+@pytest.mark.parametrize("counts", [(1, 1), (33, 700), (11_489, 1), (8000, 8191), (60_000, 9000), (100_001, 60_000)])
 def test_plan_sizes(case, counts):
     """A two-event plan at sizes on both sides of its tile changes, every rows +
     GEMM variant pinned, against the per-event evaluation."""
@@ -138,13 +138,39 @@ def test_one_column_tile(nodes, n):
         assert torch.equal(interp(h, p[:, b:b + 8192].contiguous()), got[b:b + 8192])
 
 
-# one launch against the staged kernels (which the stage timers keep): columns
-# 128 / 512, rows 96 / 320, so 1 to 16 proposals per workgroup, ragged last
-# groups, and the sizes around the largest that takes one launch
+# column counts around multiples of 32 and 64: tiles of padding columns are left out
+@pytest.mark.parametrize("q", [15, 16, 31, 32, 47, 48, 60])
+def test_column_counts(q):
+    import torch
+    cfg = wl.CFG1.with_(name="columns", seg_len=8.0, n_nodes=100, q=q)
+    h = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    n = 20_000                                        # forms its own rows
+    idx, jit = wl.node_jitter(n, cfg.n_nodes)
+    qd = wl.queries(cfg, n=n).near_nodes(h.nodes(), idx, jit)
+    p = torch.from_numpy(rbfl.params_soa(h, qd, cfg.t_trig)).cuda()
+    h.reserve(n)
+    got = interp(h, p)
+    # every output of one proposal is the weighted sum of its row (K = 2 q + 1
+    # sums of 105 products): against torch with the library's nodes and weights
+    x = (p[:4].T / torch.from_numpy(h.frame()["semi"].copy()).cuda())[:256]
+    nodes, W = torch.from_numpy(h.nodes()).cuda(), torch.from_numpy(h.weights()).cuda()
+    d2 = ((x[:, None, :] - nodes[None]) ** 2).sum(-1)
+    phi = torch.cat([torch.exp(-h.eps() ** 2 * d2), torch.ones(256, 1, device="cuda", dtype=torch.float64), x], 1)
+    assert got.shape[1] == 2 * q + 1 and W.shape == (105, 2 * q + 1)
+    bound = 105 * 8 * 2.2e-16 * (phi.abs() @ W.abs())  # rows to a few units, sums of 105 terms in any order
+    assert ((got[:256] - phi @ W).abs() <= bound).all()
+    for step in (8192, 700):                          # the other tiles: the same bits
+        for b in range(0, n, step):
+            assert torch.equal(interp(h, p[:, b:b + step].contiguous()), got[b:b + step])
+
+
+# one launch against the staged kernels (which the stage timers keep): 1 to 16
+# proposals per workgroup, one and seven tiles of 64 columns, ragged last groups,
+# and the sizes around the largest that takes one launch
 @pytest.mark.parametrize("sites, modes, nodes, degree, q, sizes", [
-    (1, 1, 60, 1, 5, [1, 2, 127, 128, 129, 255, 257, 1000, 2033, 2048, 2049]),
+    (1, 1, 60, 1, 5, [1, 2, 255, 256, 257, 1000, 2049, 4081, 4096, 4097]),
     (1, 2, 150, 3, 13, [1, 3, 65, 511]),
-    (3, 4, 300, 2, 16, [1, 31, 32, 33, 100, 255, 481, 512, 513]),
+    (3, 4, 300, 2, 16, [1, 31, 36, 37, 100, 255, 289, 575, 576, 577]),
 ])
 def test_one_launch(sites, modes, nodes, degree, q, sizes):
     import torch
