@@ -557,10 +557,19 @@ __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
   }
 }
 
+// Item of workgroup b of n: every other round of the 256 CUs is dealt backwards.
+// The items come in decreasing length and the first rounds are all resident, so
+// in order a CU that gets the longest item of one round gets that of each (12
+// events of 250 proposals: 180 to 166 us, 6 of 1000: 225 to 211).
+__device__ __forceinline__ int64_t dealt_item(int64_t b, int64_t n) {
+  const int64_t round = b >> 8;
+  return (round & 1) && ((round + 1) << 8) <= n ? (round << 8) + 255 - (b & 255) : b;
+}
+
 // The 64 x 64 tile over the work list, one workgroup per item: its items are too
 // short to wait for the counter in between.
 __global__ void __launch_bounds__(256, 2) k_ragged_gemm_mid_fp64(const EventDesc *__restrict__ ev, int n_ev) {
-  const int64_t item = blockIdx.x;
+  const int64_t item = dealt_item(blockIdx.x, gridDim.x);
   const EventDesc &d = ev[work_event(ev, n_ev, item)];
   const int local = (int)(item - d.item0);
   gemm_tile<2, 2, 8>(d.Bt, d.n, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c, local % d.tiles_c);
@@ -672,7 +681,7 @@ __global__ void __launch_bounds__(256)
 // The small tiles over the work list of a multi-event batch, one workgroup per
 // item (events in decreasing row count, so the longest items start first).
 __global__ void __launch_bounds__(256) k_ragged_gemm_small_fp64(const EventDesc *__restrict__ ev, int n_ev) {
-  const int64_t item = blockIdx.x;
+  const int64_t item = dealt_item(blockIdx.x, gridDim.x);
   const EventDesc &d = ev[work_event(ev, n_ev, item)];
   const int local = (int)(item - d.item0);
   const EvalConsts &c = *d.consts;
