@@ -768,8 +768,13 @@ void launch_ragged_contract(int variant, const EventDesc *ev, int n_ev, int64_t 
 
 void launch_ragged_epilogue(const EventDesc *ev, int n_ev, const double *params, int64_t total, double *lnl,
                             hipStream_t s) {
-  // 8 proposals per workgroup while 32 would leave CUs without one
-  if (total <= 16384)
+  // one proposal per wave while that is a few rounds of the chip (12 events of 250
+  // proposals: 160 against 166 us for the batch, of 400 200 against 203; of 1000
+  // 389 against 386), two while 32 per workgroup would leave CUs without one
+  if (total <= 8192)
+    hipLaunchKernelGGL(k_ragged_epilogue<4>, dim3((unsigned)((total + 3) / 4)), dim3(kThreads), 0, s, ev, n_ev, params,
+                       total, lnl);
+  else if (total <= 16384)
     hipLaunchKernelGGL(k_ragged_epilogue<8>, dim3((unsigned)((total + 7) / 8)), dim3(kThreads), 0, s, ev, n_ev, params,
                        total, lnl);
   else

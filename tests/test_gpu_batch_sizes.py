@@ -88,8 +88,9 @@ def test_large_tiles_agree(case, v, n):
 
 
 # two events of 243 and 19 columns: 8 and 1 tiles of 32 per 32 proposals, so the
-# plan's tiles change at 2880 and 22000 of them
-@pytest.mark.parametrize("counts", [(1, 1), (33, 700), (11_489, 1), (8000, 8191), (60_000, 9000), (100_001, 60_000)])
+# plan's tiles change at 2880 and 22000 of them, the epilogue at 8192 and 16,384
+# proposals
+@pytest.mark.parametrize("counts", [(1, 1), (33, 700), (8191, 1), (8192, 1), (11_489, 1), (8000, 8191), (60_000, 9000), (100_001, 60_000)])
 def test_plan_sizes(case, counts):
     """A two-event plan at sizes on both sides of its tile changes, every rows +
     GEMM variant pinned, against the per-event evaluation."""
