@@ -47,13 +47,12 @@ __device__ __forceinline__ double2 load_pair(SharedRow y, int i) { return double
 // and the reduction are those of the staged kernels, so ln L is the same bit for
 // bit.
 //
-// slots (a power of two): the proposals' stride in LDS.  done[y] counts the
+// slots (a power of two): the proposals' stride in LDS.  nan->done[y] counts the
 // finished workgroups and wraps to zero with the last.
 __global__ void __launch_bounds__(512, 2)
     k_eval_small(const EvalConsts *__restrict__ cp, const double *__restrict__ params, int64_t ld, int nb, int slots,
                  const double *__restrict__ nodes, const double *__restrict__ W, double *__restrict__ Y,
-                 const double2 *__restrict__ basis4, double *__restrict__ lnl, NanCount *__restrict__ nan,
-                 unsigned *__restrict__ done) {
+                 const double2 *__restrict__ basis4, double *__restrict__ lnl, NanCount *__restrict__ nan) {
   extern __shared__ double As[];     // [rows][slots], then the setups
   __shared__ YlmTerms ylm[2 * RBFL_MAX_MODES];
   __shared__ int coef_off[RBFL_MAX_DET][RBFL_MAX_MODES], sig_off[RBFL_MAX_DET];
@@ -139,7 +138,7 @@ __global__ void __launch_bounds__(512, 2)
   if (!multiplies)
     epi_setup_join(t - 256, [&](int) -> const EvalConsts & { return c; }, c.n_det, nm, cnt, su, tmp);
   else if (t == 0)
-    last = atomicInc(done + blockIdx.y, gridDim.x - 1) == gridDim.x - 1;
+    last = atomicInc(nan->done + blockIdx.y, gridDim.x - 1) == gridDim.x - 1;
   __syncthreads();
   if (!last) return;
   if (blockIdx.y == 0 && t == 0) nan->slots = (unsigned long long)nb;
@@ -172,10 +171,10 @@ int small_eval_group(const EvalConsts &hc, int64_t n) {
 
 void launch_eval_small(int slots, const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
                        int64_t n, const double *nodes, const double *W, double *Y, const double2 *basis4, double *lnl,
-                       NanCount *nan, unsigned *done, hipStream_t s) {
+                       NanCount *nan, hipStream_t s) {
   const unsigned groups = (unsigned)((n + slots - 1) / slots);
   hipLaunchKernelGGL(k_eval_small, dim3(col_tiles(hc, 64), groups), dim3(512), shared_bytes(hc, slots), s, c, params, ld,
-                     (int)n, slots, nodes, W, Y, basis4, lnl, nan, done);
+                     (int)n, slots, nodes, W, Y, basis4, lnl, nan);
   RBFL_HIP(hipGetLastError());
 }
 

@@ -27,8 +27,10 @@ void reserve(Ctx &c, int64_t n) {
   if (n <= c.cap) return;
   if (c.graph_users > 0) throw Error(RBFL_E_STATE, "the work space is captured by a sampler: it cannot grow");
   c.Y.alloc((size_t)n * c.Kp);
-  c.Bt.alloc((size_t)c.rows * rows_ld(n));
-  c.small_su.alloc(epi_setup_bytes() * (size_t)std::min<int64_t>(n, kSetupMax));
+  const size_t rows = (size_t)c.rows * rows_ld(n);
+  c.small_su = nullptr;
+  c.Bt.alloc(rows + epi_setup_bytes() / sizeof(double) * (size_t)std::min<int64_t>(n, kSetupMax));
+  c.small_su = c.Bt.p + rows;
   if (c.epi_su.p) reserve_lnl_gemm(c, n);
   c.cap = n;
   if (c.prepared[RBFL_FORM_BF16]) c.A16.alloc((size_t)c.rows * n);
@@ -214,7 +216,7 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
     const int slots = small_eval_group(c.host_consts, n);
     if (slots > 0) {
       launch_eval_small(slots, c.consts.p, c.host_consts, params, ld, n, c.nodes.p, c.W.p, c.Y.p, c.basis4.p, lnl,
-                        nan, c.small_done.p, s);
+                        nan, s);
       return true;
     }
   }
@@ -223,7 +225,7 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
     return false;
   }
   auto finish = [&](int64_t b0, int64_t nb, bool ready) {
-    return ready ? launch_epilogue_ready(c.consts.p, b0, nb, c.small_su.p, c.Y.p, c.basis4.p, lnl, s, nan)
+    return ready ? launch_epilogue_ready(c.consts.p, b0, nb, c.small_su, c.Y.p, c.basis4.p, lnl, s, nan)
                  : launch_epilogue(c.consts.p, c.host_consts, params, ld, b0, nb, c.Y.p, c.basis4.p, lnl, s, nan);
   };
   bool counted = false;
@@ -237,14 +239,14 @@ static bool eval_range(Ctx &c, const double *params, int64_t ld, int64_t n, doub
         RBFL_HIP(hipEventCreate(&e));
         c.timed_events.push_back(e);
       }
-      counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, ev, c.small_su.p));
+      counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, ev, c.small_su));
       RBFL_HIP(hipEventRecord(ev[3], s));
       c.timed.push_back(Ctx::Timed{ev[0], ev[1], 2, nb});
       c.timed.push_back(Ctx::Timed{ev[1], ev[2], 0, nb});
       c.timed.push_back(Ctx::Timed{ev[2], ev[3], 1, nb});
       continue;
     }
-    counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, nullptr, c.small_su.p));
+    counted = finish(b0, nb, contract(c, params, ld, b0, nb, form, s, nullptr, c.small_su));
   }
   return counted;
 }

@@ -1439,8 +1439,7 @@ static void build_back(const rbfl_build_spec *s, hipStream_t stream, Ctx &c, Bui
   launch_fold_spline(c.basis.p, c.n_v * c.n_modes, c.T, c.q, c.consts.p, c.basis4.p, stream);
   c.nan.alloc(1);
   launch_count_nan(nullptr, 0, c.nan.p, stream);
-  c.small_done.alloc(kSmallBlocks);
-  RBFL_HIP(hipMemsetAsync(c.small_done.p, 0, sizeof(unsigned) * c.small_done.n, stream));
+  RBFL_HIP(hipMemsetAsync(c.nan.p->done, 0, sizeof(c.nan.p->done), stream));
   RBFL_HIP(hipStreamSynchronize(stream));
   c.timing[5] = seconds_since(carry.t_all);
   if (debug_mode()) debug_check_layout(c);

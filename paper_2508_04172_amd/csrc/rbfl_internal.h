@@ -180,11 +180,13 @@ struct Mlp {
 
 // NaN ln L values of the last evaluation call: `slots` partial counts, one per
 // block of the counting kernel or, in a small batch, one per proposal; each
-// call writes all that it announces, rbfl_query sums them.
-constexpr int kNanSlots = 4096;
+// call writes all that it announces, rbfl_query sums them.  done: finished
+// workgroups per group of a one-launch evaluation, zeros between the launches.
+constexpr int kNanSlots = 4096, kSmallBlocks = 256;
 struct NanCount {
   unsigned long long slots;
   unsigned long long part[kNanSlots];
+  unsigned done[kSmallBlocks];
 };
 
 struct Ctx {
@@ -223,8 +225,7 @@ struct Ctx {
   DevBuf<double2> win_D;       // exact outputs: brute_D with the window start's phase, made on first use
   DevBuf<int4> coldesc;        // output column layout (kind, detector, mode, index), [K]
   DevBuf<NanCount> nan;        // of the last evaluation call
-  DevBuf<unsigned char> small_su;   // epilogue setups of a small batch [min(cap, kSetupMax)]
-  DevBuf<unsigned> small_done; // [kSmallBlocks] finished workgroups of a one-launch evaluation, 0 between calls
+  void *small_su = nullptr;    // epilogue setups of a small batch [min(cap, kSetupMax)], behind the rows in Bt
   // reduced-precision weight copies
   DevBuf<float> W32;           // [rows][Kp]
   DevBuf<uint16_t> W16;        // BF16 form: weights in 8-row groups [rows/8][Kp][8]
@@ -454,13 +455,11 @@ void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *p
                       const double *cscale, const void *setups, const double2 *basis4, const int4 *coldesc,
                       double *part, int64_t ldp, hipStream_t s, int variant, hipEvent_t mid);
 // FP64 ln L of n proposals in one launch (eval_small.hip), `slots` =
-// small_eval_group(n) of them per workgroup (0: n is too large); done[kSmallBlocks]
-// holds zeros between the launches, nan is filled too.
-constexpr int kSmallBlocks = 256;
+// small_eval_group(n) of them per workgroup (0: n is too large).
 int small_eval_group(const EvalConsts &hc, int64_t n);
 void launch_eval_small(int slots, const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
                        int64_t n, const double *nodes, const double *W, double *Y, const double2 *basis4, double *lnl,
-                       NanCount *nan, unsigned *done, hipStream_t s);
+                       NanCount *nan, hipStream_t s);
 // The NaN entries of lnl[0, n), one partial count per block.
 void launch_count_nan(const double *lnl, int64_t n, NanCount *nan, hipStream_t s);
 // The nbase monomials (graded-lexicographic, variable indices poly[p][0..2],

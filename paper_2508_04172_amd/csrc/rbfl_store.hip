@@ -397,8 +397,7 @@ void load(const char *path, hipStream_t st, Ctx &c) {
   upload(c.coldesc, cd, st);
   c.nan.alloc(1);
   launch_count_nan(nullptr, 0, c.nan.p, st);
-  c.small_done.alloc(kSmallBlocks);
-  RBFL_HIP(hipMemsetAsync(c.small_done.p, 0, sizeof(unsigned) * c.small_done.n, st));
+  RBFL_HIP(hipMemsetAsync(c.nan.p->done, 0, sizeof(c.nan.p->done), st));
   RBFL_HIP(hipStreamSynchronize(st));
   if (debug_mode()) debug_check_layout(c);
 }
