@@ -400,8 +400,9 @@ int32_t rbfl_variants(int32_t form);
 
 /* Pins the contraction tile variant of `form` (0 <= variant <
  * rbfl_variants(form)) instead of the autotuner's choice.  FP64 variants are
- * tile shapes of one arithmetic (ln L identical); split-form variants are
- * digit counts (S = 5 + variant).  RBFL_E_STATE if the form is not prepared;
+ * tile shapes of one arithmetic (ln L identical; batches of fewer than 22000
+ * output tiles of 32 x 32 run smaller tiles in their place); split-form
+ * variants are digit counts (S = 5 + variant).  RBFL_E_STATE if the form is not prepared;
  * needs exclusive use of the handle. */
 int32_t rbfl_set_variant(rbfl_handle h, int32_t form, int32_t variant);
 
@@ -446,7 +447,8 @@ int32_t rbfl_fuse_epilogue(rbfl_handle h, int32_t on);
  * (the caller's; the handle's second stream for pipelined epilogues; with
  * ln L inside the contraction the stages are setups + basis rows, the
  * contraction, and the sum of its partials); RBFL_Q_KERNEL_STATS reports the
- * sums.  Not for use under graph capture. */
+ * sums.  The smallest FP64 batches, otherwise one launch, run stage by stage
+ * too (ln L identical).  Not for use under graph capture. */
 int32_t rbfl_profile(rbfl_handle h, int32_t on);
 
 /*
