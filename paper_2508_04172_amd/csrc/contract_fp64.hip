@@ -16,10 +16,9 @@
 // v_mfma_f64_16x16x4f64 (lane l holds A[l%16][l/16], B[l/16][l%16];
 // accumulator element i is D[l/16 + 4i][l%16], measured on gfx950); row
 // chunks of KC rows of both operands staged through LDS, double-buffered.
-#include <algorithm>
-
 #include "basis_rows.h"
 #include "epilogue_setup.h"
+#include "fp64_parts.h"
 #include "rbfl_internal.h"
 
 namespace rbfl {
@@ -110,9 +109,11 @@ __device__ __forceinline__ int64_t xcd_logical_block(int64_t b, int64_t nblk) {
 }
 
 // One output tile of Y[q][c] = sum_r Bt[r][q] W[r][c]: proposals tq*QT ..,
-// columns tc*CW ..; called by every thread of the workgroup.
+// columns tc*CW ..; called by every thread of the workgroup.  Entries of a row
+// from read_end on (even, at least nb) are not read and count as zeros.
 template <int RT, int CT, int KC, int WQ = 2, int WC = 2>
-__device__ __forceinline__ void gemm_tile(const double *__restrict__ Bt, int64_t nb, int64_t ldb, int rows,
+__device__ __forceinline__ void gemm_tile(const double *__restrict__ Bt, int64_t nb, int64_t read_end, int64_t ldb,
+                                          int rows,
                                           const double *__restrict__ W, int Kp, double *__restrict__ Y, int64_t tq,
                                           int tc) {
   constexpr int QT = WQ * RT * 16, CW = WC * CT * 16, NT = 64 * WQ * WC;
@@ -135,7 +136,7 @@ __device__ __forceinline__ void gemm_tile(const double *__restrict__ Bt, int64_t
     const int e = tid + u * NT;
     const int k = e / (QT / 2), q2 = e % (QT / 2);
     pa[u] = Bt + (int64_t)k * ldb + q0 + 2 * q2;
-    va[u] = q0 + 2 * q2 < ldb;
+    va[u] = q0 + 2 * q2 < read_end;
   }
 #pragma unroll
   for (int u = 0; u < LW; ++u) {
@@ -217,10 +218,10 @@ __device__ __forceinline__ void gemm_tile(const double *__restrict__ Bt, int64_t
 // WQ x WC waves per workgroup.
 template <int RT, int CT, int KC, int WQ, int WC>
 __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
-    k_gemm_fp64(const double *__restrict__ Bt, int64_t nb, int64_t ldb, int rows, const double *__restrict__ W,
-                int Kp, int n_ct, double *__restrict__ Y) {
+    k_gemm_fp64(const double *__restrict__ Bt, int64_t nb, int64_t read_end, int64_t ldb, int rows,
+                const double *__restrict__ W, int Kp, int n_ct, double *__restrict__ Y) {
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
-  gemm_tile<RT, CT, KC, WQ, WC>(Bt, nb, ldb, rows, W, Kp, Y, tile / n_ct, (int)(tile % n_ct));
+  gemm_tile<RT, CT, KC, WQ, WC>(Bt, nb, read_end, ldb, rows, W, Kp, Y, tile / n_ct, (int)(tile % n_ct));
 }
 
 constexpr int kFormRowsQ = 64;   // proposals per workgroup of k_rows_gemm_fp64
@@ -552,7 +553,7 @@ __global__ void __launch_bounds__(64 * WQ * WC, 512 / (64 * WQ * WC))
     if (item >= total_items) break;
     const EventDesc &d = ev[work_event(ev, n_ev, item)];
     const int64_t local = item - d.item0;
-    gemm_tile<RT, CT, KC, WQ, WC>(d.Bt, d.n, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c,
+    gemm_tile<RT, CT, KC, WQ, WC>(d.Bt, d.n, d.ldb, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c,
                                   (int)(local % d.tiles_c));
   }
 }
@@ -572,7 +573,7 @@ __global__ void __launch_bounds__(256, 2) k_ragged_gemm_mid_fp64(const EventDesc
   const int64_t item = dealt_item(blockIdx.x, gridDim.x);
   const EventDesc &d = ev[work_event(ev, n_ev, item)];
   const int local = (int)(item - d.item0);
-  gemm_tile<2, 2, 8>(d.Bt, d.n, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c, local % d.tiles_c);
+  gemm_tile<2, 2, 8>(d.Bt, d.n, d.ldb, d.ldb, d.rows, d.W, d.Kp, d.Y, local / d.tiles_c, local % d.tiles_c);
 }
 
 __global__ void k_zero_item_counter(unsigned long long *counter) {
@@ -593,7 +594,7 @@ int gemm_rows(const EvalConsts &hc, int kc) { return (hc.N + hc.M + kc - 1) / kc
 // bit for bit.
 constexpr int kTinyTile = 32, kTinyKC = 16;
 constexpr int kTinyPad = 16;   // doubles per LDS row: two of a fragment's four rows per bank set
-__device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, int nb, int64_t ldb, int rows,
+__device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, int nb, int end, int64_t ldb, int rows,
                                                 const double *__restrict__ W, int Kp, double *__restrict__ Y, int q0,
                                                 int c0) {
   constexpr int T = kTinyTile, KC = kTinyKC, KS = KC / 4, D = 4;
@@ -603,8 +604,7 @@ __device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, i
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wq = wave & 1, wc = wave >> 1, kk = lane >> 4, ll = lane & 15;
   const int sk = tid / (T / 2), sm = 2 * (tid % (T / 2));
-  // proposals past the batch (padded to 8) re-read its last pair: their outputs are not stored
-  const int end = (nb + 7) & ~7;
+  // from entry `end` of a row on (even, at least nb) its last pair is read again: those outputs are not stored
   const double *pa = Bt + (int64_t)sk * ldb + (q0 + sm < end ? q0 + sm : end - 2);
   const double *pw = W + (int64_t)sk * Kp + c0 + sm;
   const int64_t stepA = KC * ldb, stepW = (int64_t)KC * Kp;
@@ -672,10 +672,10 @@ __device__ __forceinline__ void gemm_small_tile(const double *__restrict__ Bt, i
 }
 
 __global__ void __launch_bounds__(256)
-    k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int64_t ldb, int rows, const double *__restrict__ W,
-                      int Kp, int n_ct, double *__restrict__ Y) {
+    k_gemm_small_fp64(const double *__restrict__ Bt, int nb, int end, int64_t ldb, int rows,
+                      const double *__restrict__ W, int Kp, int n_ct, double *__restrict__ Y) {
   const int64_t tile = xcd_logical_block(blockIdx.x, gridDim.x);
-  gemm_small_tile(Bt, nb, ldb, rows, W, Kp, Y, (int)(tile / n_ct) * kTinyTile, (int)(tile % n_ct) * kTinyTile);
+  gemm_small_tile(Bt, nb, end, ldb, rows, W, Kp, Y, (int)(tile / n_ct) * kTinyTile, (int)(tile % n_ct) * kTinyTile);
 }
 
 // The small tiles over the work list of a multi-event batch, one workgroup per
@@ -686,7 +686,7 @@ __global__ void __launch_bounds__(256) k_ragged_gemm_small_fp64(const EventDesc 
   const int local = (int)(item - d.item0);
   const EvalConsts &c = *d.consts;
   const int rows = (c.N + c.M + 2 * kTinyKC - 1) / (2 * kTinyKC) * (2 * kTinyKC);
-  gemm_small_tile(d.Bt, (int)d.n, d.ldb, rows, d.W, d.Kp, d.Y, local / d.tiles_c * kTinyTile,
+  gemm_small_tile(d.Bt, (int)d.n, (int)d.ldb, d.ldb, rows, d.W, d.Kp, d.Y, local / d.tiles_c * kTinyTile,
                   local % d.tiles_c * kTinyTile);
 }
 
@@ -695,59 +695,29 @@ __global__ void __launch_bounds__(256) k_ragged_gemm_small_fp64(const EventDesc 
 int basis_rows_written(const EvalConsts &hc) { return (hc.N + hc.M + 15) / 16 * 16; }
 
 template <int RT, int CT, int KC, int WQ = 2, int WC = 2>
-void launch_gemm(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc, const double *W, double *Y,
-                 hipStream_t s) {
+void launch_gemm(const double *Bt, const Fp64Part &part, int64_t ldb, const EvalConsts &hc, const double *W,
+                 double *Y, hipStream_t s) {
   constexpr int QT = WQ * RT * 16, CW = WC * CT * 16;
   static_assert(kColTile % CW == 0 && kRowChunk % KC == 0 && 16 % KC == 0, "K and the rows are padded to whole tiles");
   const int n_ct = col_tiles(hc, CW);
-  const int64_t nblk = (nb + QT - 1) / QT * n_ct;
-  hipLaunchKernelGGL((k_gemm_fp64<RT, CT, KC, WQ, WC>), dim3((unsigned)nblk), dim3(64 * WQ * WC), 0, s, Bt, nb, ldb,
-                     gemm_rows(hc, KC), W, hc.Kp, n_ct, Y);
+  const int64_t nblk = (part.count + QT - 1) / QT * n_ct;
+  hipLaunchKernelGGL((k_gemm_fp64<RT, CT, KC, WQ, WC>), dim3((unsigned)nblk), dim3(64 * WQ * WC), 0, s,
+                     Bt + part.first, part.count, part.read_end, ldb, gemm_rows(hc, KC), W, hc.Kp, n_ct,
+                     Y + part.first * hc.Kp);
   RBFL_HIP(hipGetLastError());
 }
 
-void launch_gemm_small(const double *Bt, int64_t nb, int64_t ldb, const EvalConsts &hc, const double *W, double *Y,
-                       hipStream_t s) {
+void launch_gemm_small(const double *Bt, const Fp64Part &part, int64_t ldb, const EvalConsts &hc, const double *W,
+                       double *Y, hipStream_t s) {
   static_assert(kColTile % kTinyTile == 0 && kRowChunk % (2 * kTinyKC) == 0, "whole tiles and chunk pairs");
   const int n_ct = col_tiles(hc, kTinyTile);
-  const int64_t nblk = (nb + kTinyTile - 1) / kTinyTile * n_ct;
-  hipLaunchKernelGGL(k_gemm_small_fp64, dim3((unsigned)nblk), dim3(256), 0, s, Bt, (int)nb, ldb,
-                     gemm_rows(hc, 2 * kTinyKC), W, hc.Kp, n_ct, Y);
+  const int64_t nblk = (part.count + kTinyTile - 1) / kTinyTile * n_ct;
+  hipLaunchKernelGGL(k_gemm_small_fp64, dim3((unsigned)nblk), dim3(256), 0, s, Bt + part.first, (int)part.count,
+                     (int)part.read_end, ldb, gemm_rows(hc, 2 * kTinyKC), W, hc.Kp, n_ct, Y + part.first * hc.Kp);
   RBFL_HIP(hipGetLastError());
 }
 
 }  // namespace
-
-// Tiles of the FP64 contraction by a batch's count of 32 x 32 output tiles: below
-// kTinyTiles 32 x 32 (k_gemm_small_fp64), below kMidTiles 64 x 64 (variant 4's),
-// from there on the handle's variant.  A large tile waits for one workgroup's
-// chain of chunks while there is less than a round of them (64 x 128, 808 rows:
-// 75-79 us for 512 to 1021 proposals of 1280 columns, 33 and 50 us with 32 x 32
-// tiles), and its last rounds are coarse; a wave with one 16 x 16 tile reads as
-// much LDS as it multiplies.  us for 32 x 32 / 64 x 64 / best large tile, 808
-// rows x 1280 columns: 88 / 95 / 117 at 2048 proposals (2560 tiles), 129 / 118 /
-// 118 at 3000 (3760), 331 / 288 / 316 at 8192, 633 / 519 / 526 at 16384 (20480);
-// 3008 rows x 2560 columns: 299 / 329 / 411 at 1021 (2560), 435 / 408 / 413 at
-// 1500 (3760), 1138 / 982 / 1152 at 4000, 2343 / 1922 / 1921 at 8192 (20480).
-// All give the same bits.
-constexpr int64_t kTinyTiles = 2880, kMidTiles = 22000;
-static int64_t tiles32(const EvalConsts &hc, int64_t nb) { return (nb + 31) / 32 * col_tiles(hc, 32); }
-
-// How many of a batch's first proposals the variant's tile takes; the rest goes
-// to the smaller ones.  None below kMidTiles.  The 8-wave tiles (256 x 128, one
-// workgroup per CU; 128 x 128, two) leave half the chip idle in a short last
-// round, so they hand it over where the smaller tiles take less: with two per CU
-// up to 0.4 of a round (which would cost half of one) and from 0.5 to 0.75 (a
-// whole one): 7.30 to 6.84 ms at 30011 proposals of 3008 rows and 2560 columns
-// (9.2 rounds).
-static int64_t main_part(const EvalConsts &hc, int64_t nb, int variant) {
-  if (tiles32(hc, nb) < kMidTiles) return 0;
-  if (variant != 5 && variant != 6) return nb;
-  const int64_t qt = variant == 5 ? 256 : 128, round = variant == 5 ? 256 : 512, n_ct = hc.Kp / 128;
-  const int64_t tiles = (nb + qt - 1) / qt * n_ct, rest = tiles % round;
-  const bool hand_over = 4 * rest < 3 * round && (variant == 5 || 5 * rest < 2 * round || 2 * rest > round);
-  return hand_over ? std::min(nb, (tiles - rest) / n_ct * qt) : nb;
-}
 
 // Rows that a batch's contraction with `variant` (-1: the fused epilogue's) reads
 // and the row kernels must write: whole chunk pairs where 32 x 32 tiles take a part.
@@ -761,8 +731,6 @@ static int rows_needed(const EvalConsts &hc, int64_t nb, int variant) {
 // plan's variant (64 x 64 / variant: 129 / 145 us for 4 events of 1000 proposals,
 // 4096 tiles; 385 / 400 us for 12, 11,440 tiles).
 int ragged_small_tile(int64_t tiles) { return tiles < kTinyTiles ? 1 : tiles < kMidTiles ? 2 : 0; }
-
-int64_t rows_ld(int64_t n) { return (n + 7) & ~int64_t(7); }
 
 int gemm_lnl_col_tile() { return kLnlWC * kLnlCT * 16; }
 
@@ -891,21 +859,20 @@ void launch_ragged_gemm_small_fp64(int small, const EventDesc *ev, int n_ev, int
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
                       int variant) {
   if (variant < 0 || variant >= gemm_fp64_variants()) throw Error(RBFL_E_INVALID_ARG, "unknown FP64 GEMM variant");
-  const int64_t ldb = rows_ld(nb), n1 = main_part(hc, nb, variant), n2 = nb - n1;
-  if (n1 > 0) switch (variant) {
-      case 0: launch_gemm<2, 4, 8>(Bt, n1, ldb, hc, W, Y, s); break;
-      case 1: launch_gemm<4, 2, 8>(Bt, n1, ldb, hc, W, Y, s); break;
-      case 2: launch_gemm<2, 4, 16>(Bt, n1, ldb, hc, W, Y, s); break;
-      case 3: launch_gemm<4, 2, 16>(Bt, n1, ldb, hc, W, Y, s); break;
-      case 4: launch_gemm<2, 2, 8>(Bt, n1, ldb, hc, W, Y, s); break;
-      case 5: launch_gemm<4, 4, 8, 4, 2>(Bt, n1, ldb, hc, W, Y, s); break;
-      default: launch_gemm<2, 4, 8, 4, 2>(Bt, n1, ldb, hc, W, Y, s);
+  const int64_t ldb = rows_ld(nb);
+  const Fp64Parts p = fp64_parts(hc, nb, variant);
+  if (p.main.count > 0) switch (variant) {
+      case 0: launch_gemm<2, 4, 8>(Bt, p.main, ldb, hc, W, Y, s); break;
+      case 1: launch_gemm<4, 2, 8>(Bt, p.main, ldb, hc, W, Y, s); break;
+      case 2: launch_gemm<2, 4, 16>(Bt, p.main, ldb, hc, W, Y, s); break;
+      case 3: launch_gemm<4, 2, 16>(Bt, p.main, ldb, hc, W, Y, s); break;
+      case 4: launch_gemm<2, 2, 8>(Bt, p.main, ldb, hc, W, Y, s); break;
+      case 5: launch_gemm<4, 4, 8, 4, 2>(Bt, p.main, ldb, hc, W, Y, s); break;
+      default: launch_gemm<2, 4, 8, 4, 2>(Bt, p.main, ldb, hc, W, Y, s);
     }
-  if (n2 <= 0) return;
-  Bt += n1;
-  Y += n1 * hc.Kp;
-  if (tiles32(hc, n2) < kTinyTiles) launch_gemm_small(Bt, n2, ldb, hc, W, Y, s);
-  else launch_gemm<2, 2, 8>(Bt, n2, ldb, hc, W, Y, s);
+  if (p.rest.count <= 0) return;
+  if (tiles32(hc, p.rest.count) < kTinyTiles) launch_gemm_small(Bt, p.rest, ldb, hc, W, Y, s);
+  else launch_gemm<2, 2, 8>(Bt, p.rest, ldb, hc, W, Y, s);
 }
 
 bool launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,

@@ -362,7 +362,8 @@ const char *contract_variant_name(int form, int variant);
 // (nothing reads Y past column K).
 inline int col_tiles(const EvalConsts &hc, int width) { return (hc.K + width - 1) / width; }
 // ---- FP64 rows + GEMM (contract_fp64.hip) ----
-int64_t rows_ld(int64_t n);
+// Leading dimension of the basis rows of n proposals; they hold zeros from n on.
+inline int64_t rows_ld(int64_t n) { return (n + 7) & ~int64_t(7); }
 int gemm_fp64_variants();
 const char *gemm_fp64_variant_name(int variant);
 double gemm_fp64_reuse(int variant);
