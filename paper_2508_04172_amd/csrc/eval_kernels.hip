@@ -355,6 +355,10 @@ __global__ void __launch_bounds__(kThreads) k_epilogue_banded(const EvalConsts *
     N0[wave][pr] = in ? (int)fl : 4;
     F[wave][pr] = s - fl;
   }
+  // written by one lane, read by others: LDS of one wave, so its order is all it takes
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (!__all(ok ? 1 : 0)) {
     put(-__builtin_huge_val());
     return;
