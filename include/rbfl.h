@@ -366,7 +366,9 @@ int32_t rbfl_query(rbfl_handle h, int32_t what, void *out, size_t bytes);
 /* Tile autotuner: times each contraction tile variant of `form` on the
  * first min(n, work capacity) proposals of `params` (device [11][n]) with HIP
  * events on `stream` and keeps the fastest for this handle (RBFL_Q_TUNE
- * reports the timings).  Split-form variants differ in digit count S (5..8,
+ * reports the timings).  FP64 tiles that evaluations of this batch do not run
+ * (rbfl_set_variant) are timed but not kept: the handle keeps the tile it had,
+ * unless the fused variant is faster than what the batch does run.  Split-form variants differ in digit count S (5..8,
  * variant v has S = 5 + v): only those whose ln L on these proposals stays
  * within the handle's split tolerance (rbfl_set_split_tol, default
  * RBFL_SPLIT_TOL) of the FP64 form's (and keeps its domain flags) are
@@ -400,8 +402,10 @@ int32_t rbfl_variants(int32_t form);
 
 /* Pins the contraction tile variant of `form` (0 <= variant <
  * rbfl_variants(form)) instead of the autotuner's choice.  FP64 variants are
- * tile shapes of one arithmetic (ln L identical; batches of fewer than 22000
- * output tiles of 32 x 32 run smaller tiles in their place); split-form
+ * tile shapes of one arithmetic (ln L identical).  Batches of fewer than 22000
+ * output tiles of 32 x 32 run smaller tiles in their place, and with at most 128
+ * outputs batches from 12288 proposals on (32768 with more than 512 rows) a
+ * kernel that forms its own rows, whatever the tile pinned.  Split-form
  * variants are digit counts (S = 5 + variant).  RBFL_E_STATE if the form is not prepared;
  * needs exclusive use of the handle. */
 int32_t rbfl_set_variant(rbfl_handle h, int32_t form, int32_t variant);
@@ -461,14 +465,15 @@ int32_t rbfl_profile(rbfl_handle h, int32_t on);
  * proposals in columns [sum_{e'<e} counts[e'], ...)) and lnl (FP64 [total]).
  * Execution: one launch writes the FP64 basis rows of every event; a
  * persistent FP64 GEMM kernel then takes (event, proposal tile, column tile)
- * items, events ordered by decreasing row count N + M, from an
+ * items, events ordered by decreasing row count (N + M padded to 32), from an
  * atomic counter (reset by a kernel); then the epilogue finishes ln L of each
  * proposal with its own event's frame and basis.  Variants 0-2 instead form
- * the rows inside the persistent contraction (fused), variants 3-4 are the
+ * the rows inside the persistent contraction (fused), variants 3-5 are the
  * rows + GEMM tiles (the default; a batch of fewer than 22000 output tiles of
  * 32 x 32 runs smaller tiles, one workgroup per item, in their place, with the
- * same results).  RBFL_PLAN_AUTOTUNE times each variant on
- * the whole batch (HIP events) and keeps the fastest; RBFL_PLAN_GRAPH captures
+ * same results).  RBFL_PLAN_AUTOTUNE times each variant, with its own tile, on
+ * the whole batch (HIP events) and keeps the fastest (in such a small batch the
+ * smaller tiles, reported as variant 3, or a fused variant); RBFL_PLAN_GRAPH captures
  * the launch in a HIP graph, replayed by rbfl_plan_launch -- a sampler step
  * writes new proposals into `params` and launches again, without
  * re-capturing.  The handles must outlive the plan; plan creation allocates

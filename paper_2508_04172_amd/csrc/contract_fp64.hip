@@ -721,9 +721,9 @@ void launch_gemm_small(const double *Bt, const Fp64Part &part, int64_t ldb, cons
 
 // Rows that a batch's contraction with `variant` (-1: the fused epilogue's) reads
 // and the row kernels must write: whole chunk pairs where 32 x 32 tiles take a part.
-static int rows_needed(const EvalConsts &hc, int64_t nb, int variant) {
+static int rows_needed(const EvalConsts &hc, int64_t nb, int variant, bool pinned) {
   if (variant < 0) return basis_rows_written(hc);
-  const int64_t rest = nb - main_part(hc, nb, variant);
+  const int64_t rest = fp64_parts(hc, nb, variant, pinned).rest.count;
   return rest > 0 && tiles32(hc, rest) < kTinyTiles ? hc.rows : basis_rows_written(hc);
 }
 
@@ -797,9 +797,10 @@ void launch_rows_gemm_fp64(const EvalConsts *c, const EvalConsts &hc, const doub
 }
 
 bool launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups) {
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups,
+                      bool pinned) {
   const int64_t ldb = rows_ld(nb);
-  const int n_rows = rows_needed(hc, nb, variant);
+  const int n_rows = rows_needed(hc, nb, variant, pinned);
   // one value per thread while that is fewer than four rounds of the chip
   // (1021 proposals of 832 rows: 9.1 against 10.7 us; 2048: no gain)
   if (ldb * n_rows <= (1 << 20)) {
@@ -857,10 +858,10 @@ void launch_ragged_gemm_small_fp64(int small, const EventDesc *ev, int n_ev, int
 }
 
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
-                      int variant) {
+                      int variant, bool pinned) {
   if (variant < 0 || variant >= gemm_fp64_variants()) throw Error(RBFL_E_INVALID_ARG, "unknown FP64 GEMM variant");
   const int64_t ldb = rows_ld(nb);
-  const Fp64Parts p = fp64_parts(hc, nb, variant);
+  const Fp64Parts p = fp64_parts(hc, nb, variant, pinned);
   if (p.main.count > 0) switch (variant) {
       case 0: launch_gemm<2, 4, 8>(Bt, p.main, ldb, hc, W, Y, s); break;
       case 1: launch_gemm<4, 2, 8>(Bt, p.main, ldb, hc, W, Y, s); break;
@@ -877,15 +878,20 @@ void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const 
 
 bool launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
-                         int variant, hipEvent_t mid, void *setups) {
-  const int64_t own = gemm_own_rows(hc, nb);
+                         int variant, hipEvent_t mid, void *setups, bool pinned) {
+  const int64_t own = pinned ? 0 : gemm_own_rows(hc, nb);
   bool ready = false;
   if (own < nb)
-    ready = launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s, variant, own == 0 ? setups : nullptr);
+    ready = launch_rows_fp64(c, hc, params, ld, b0 + own, nb - own, nodes, Bt, s, variant, own == 0 ? setups : nullptr,
+                             pinned);
   if (mid) RBFL_HIP(hipEventRecord(mid, s));
   if (own > 0) launch_rows_gemm_fp64(c, hc, params, ld, b0, own, nodes, W, Y, s);
-  if (own < nb) launch_gemm_fp64(Bt, nb - own, hc, W, Y + own * hc.Kp, s, variant);
+  if (own < nb) launch_gemm_fp64(Bt, nb - own, hc, W, Y + own * hc.Kp, s, variant, pinned);
   return ready;
+}
+
+bool gemm_fp64_variant_runs(const EvalConsts &hc, int64_t nb, int variant) {
+  return main_part(hc, nb - gemm_own_rows(hc, nb), variant) > 0;
 }
 
 }  // namespace rbfl

@@ -739,8 +739,8 @@ void launch_contract_fp32(const EvalConsts *c, const EvalConsts &hc, const doubl
 }
 
 
-// Multi-event variants: 0-2 the fused persistent kernel, 3-4 basis rows +
-// persistent GEMM (64 x 128 tiles, 8- and 16-row chunks).
+// Multi-event variants: 0-2 the fused persistent kernel, 3-5 basis rows +
+// persistent GEMM (64 x 128 tiles with 8- and 16-row chunks, 128 x 128 tiles).
 int ragged_variants() { return 6; }
 int ragged_fused_variants() { return 3; }
 int ragged_blocks_per_cu(int variant) { return variant < 3 ? 2 : variant == 3 ? 4 : variant == 4 ? 3 : 2; }

@@ -50,8 +50,9 @@ struct Fp64Part {
 struct Fp64Parts {
   Fp64Part main, rest;      // the variant's tile; the smaller ones
 };
-inline Fp64Parts fp64_parts(const EvalConsts &hc, int64_t nb, int variant) {
-  const int64_t n1 = main_part(hc, nb, variant);   // a whole number of tiles, or the batch
+// pinned: the variant's tile takes the whole batch whatever its size.
+inline Fp64Parts fp64_parts(const EvalConsts &hc, int64_t nb, int variant, bool pinned) {
+  const int64_t n1 = pinned ? nb : main_part(hc, nb, variant);   // a whole number of tiles, or the batch
   return {{0, n1, rows_ld(n1)}, {n1, nb - n1, rows_ld(nb - n1)}};
 }
 

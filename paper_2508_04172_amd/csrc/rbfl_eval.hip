@@ -46,7 +46,7 @@ void reserve(Ctx &c, int64_t n) {
 }
 
 static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
-                     hipEvent_t *marks = nullptr, void *setups = nullptr);
+                     hipEvent_t *marks = nullptr, void *setups = nullptr, bool pinned = false);
 
 // True when `s` is being captured into a graph (or its capture state cannot
 // be read): the pipelined order forks onto a second stream, so such calls
@@ -263,8 +263,9 @@ void eval(Ctx &c, const double *params, int64_t n, double *lnl, int form, hipStr
 // stages where the form has them (basis rows, then the MFMA product); marks,
 // when given, are recorded before, between and after the stages.  Returns
 // whether the epilogue's setups have been formed too (into setups, when given).
+// pinned: the FP64 form's tile variant whatever the batch size.
 static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,
-                     hipEvent_t *marks, void *setups) {
+                     hipEvent_t *marks, void *setups, bool pinned) {
   bool ready = false;
   auto mark = [&](int i) {
     if (marks) RBFL_HIP(hipEventRecord(marks[i], s));
@@ -273,7 +274,7 @@ static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64
     const int v = c.variant[RBFL_FORM_FP64];
     if (v < gemm_fp64_variants()) {
       ready = launch_product_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Bt.p, c.Y.p, s, v,
-                                  marks ? marks[1] : nullptr, setups);
+                                  marks ? marks[1] : nullptr, setups, pinned);
     } else {
       mark(1);
       launch_contract_fp64(c.consts.p, c.host_consts, params, ld, b0, nb, c.nodes.p, c.W.p, c.Y.p, s, 2);
@@ -329,9 +330,6 @@ void interp(Ctx &c, const double *params, int64_t n, double *out, int form, hipS
   }
 }
 
-// Times every contraction tile variant of `form` on the first min(n, work
-// capacity) proposals of `params` (HIP events, median of 3 after a warm-up)
-// and keeps the fastest for later rbfl_eval/rbfl_interp calls.
 // ln L of the first nb proposals with the current variant of `form`, to host.
 static std::vector<double> lnl_probe(Ctx &c, const double *params, int64_t n, int64_t nb, int form, double *dev,
                                      hipStream_t s) {
@@ -343,6 +341,13 @@ static std::vector<double> lnl_probe(Ctx &c, const double *params, int64_t n, in
   return h;
 }
 
+// Times every contraction tile variant of `form` on the first min(n, work
+// capacity) proposals of `params` (HIP events, median of 3 after a warm-up)
+// and keeps the fastest for later rbfl_eval/rbfl_interp calls.  An FP64 tile
+// that evaluations of this batch would not run (they take smaller tiles, or form
+// their own rows) is timed all the same but not kept: where no tile is run, the
+// handle keeps the tile it had, for the larger batches that do run it, unless the
+// fused variant is faster than what this batch does run.
 void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) {
   require(params != nullptr && n >= 1, "autotune needs proposals");
   if (form < 0 || form > RBFL_FORM_SPLIT) throw Error(RBFL_E_INVALID_ARG, "unknown or untunable form");
@@ -350,6 +355,18 @@ void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) 
   if (c.cap == 0) reserve(c, std::min<int64_t>(n, 65536));
   const int64_t nb = std::min(c.cap, n);
   const int nv = contract_variants(form);
+  const int n_tiles = form == RBFL_FORM_FP64 ? gemm_fp64_variants() : 0;
+  const int before = c.variant[form] < n_tiles ? c.variant[form] : 0;
+  bool runs[8];
+  bool by_size = n_tiles > 0;     // no tile variant runs: one more candidate, what the rules on sizes run
+  for (int v = 0; v < 8; ++v) {
+    runs[v] = v >= n_tiles || gemm_fp64_variant_runs(c.host_consts, nb, v);
+    by_size = by_size && (v >= n_tiles || !runs[v]);
+  }
+  auto run = [&](int v) {         // v = nv: by the rules on sizes
+    c.variant[form] = v < nv ? v : before;
+    contract(c, params, n, 0, nb, form, s, nullptr, nullptr, v < nv && !runs[v]);
+  };
   // The split form's slice count sets its accuracy: a variant is eligible
   // only if its ln L stays within split_tol of the FP64 form's on these
   // proposals (same domain flags, finite entries compared).
@@ -382,20 +399,20 @@ void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) 
       c.split_err[v] = err;
       eligible[v] = err <= c.split_tol;
     }
-    contract(c, params, n, 0, nb, form, s);
+    run(v);
   }
+  if (by_size) run(nv);
   // two interleaved rounds of three timed launches per variant (so that no
   // variant is timed alone while the clocks settle); keep each variant's
   // smaller round median
-  double med[8];
-  for (int v = 0; v < 8; ++v) med[v] = 1e300;
+  double med[9];
+  for (double &m : med) m = 1e300;
   for (int round = 0; round < 2; ++round)
-    for (int v = 0; v < nv && v < 8; ++v) {
-      c.variant[form] = v;
+    for (int v = 0; v < nv + (by_size ? 1 : 0); ++v) {
       double t[3];
       for (int r = 0; r < 3; ++r) {
         RBFL_HIP(hipEventRecord(e0, s));
-        contract(c, params, n, 0, nb, form, s);
+        run(v);
         RBFL_HIP(hipEventRecord(e1, s));
         RBFL_HIP(hipEventSynchronize(e1));
         float ms = 0.0f;
@@ -407,18 +424,19 @@ void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) 
     }
   for (int v = 0; v < nv && v < 8; ++v) {
     c.tune_ms[form][v] = med[v];
-    if (eligible[v] && med[v] < best_ms) {
+    if (eligible[v] && runs[v] && med[v] < best_ms) {
       best_ms = med[v];
       best = v;
     }
   }
+  if (by_size && med[nv] <= best_ms) best = before;
   // FP64 GEMM tiles within 3% of the fastest time: keep the one whose larger
   // workgroup tile re-reads the least (the difference is within run-to-run
   // noise, about 2-3% between launches of the same tile; the bandwidth saved,
   // up to 3x, is not)
-  if (form == RBFL_FORM_FP64 && best >= 0 && best < gemm_fp64_variants()) {
-    for (int v = 0; v < gemm_fp64_variants() && v < nv && v < 8; ++v)
-      if (med[v] <= 1.03 * best_ms && gemm_fp64_reuse(v) > gemm_fp64_reuse(best)) best = v;
+  if (!by_size && best >= 0 && best < n_tiles) {
+    for (int v = 0; v < n_tiles; ++v)
+      if (runs[v] && med[v] <= 1.03 * best_ms && gemm_fp64_reuse(v) > gemm_fp64_reuse(best)) best = v;
   }
   if (best < 0) {
     // no split variant within split_tol: keep the most accurate one

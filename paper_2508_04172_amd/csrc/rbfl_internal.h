@@ -371,17 +371,22 @@ double gemm_fp64_reuse(int variant);
 // gemm_fp64_variants()): basis rows into Bt and their contraction, or in one
 // kernel where that is better; mid, when given, is recorded between the two.
 // setups, when given, holds min(nb, kSetupMax) epilogue setups; returns whether
-// they have been formed too (small batches).
+// they have been formed too (small batches).  pinned: with the variant's own
+// tile at any batch size (the autotuner's timings), else by the rules on sizes.
 constexpr int kSetupMax = 4096;
 bool launch_product_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                          int64_t nb, const double *nodes, const double *W, double *Bt, double *Y, hipStream_t s,
-                         int variant, hipEvent_t mid, void *setups = nullptr);
+                         int variant, hipEvent_t mid, void *setups = nullptr, bool pinned = false);
+// Whether a batch of nb proposals runs `variant`'s tile at all (small batches
+// take smaller ones, a single column tile forms its own rows).
+bool gemm_fp64_variant_runs(const EvalConsts &hc, int64_t nb, int variant);
 bool launch_rows_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
-                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups = nullptr);
+                      int64_t nb, const double *nodes, double *Bt, hipStream_t s, int variant, void *setups = nullptr,
+                      bool pinned = false);
 bool launch_epilogue_ready(const EvalConsts *c, int64_t b0, int64_t nb, const void *setups, const double *Y,
                            const double2 *basis, double *lnl, hipStream_t s, NanCount *nan);
 void launch_gemm_fp64(const double *Bt, int64_t nb, const EvalConsts &hc, const double *W, double *Y, hipStream_t s,
-                      int variant);
+                      int variant, bool pinned);
 void launch_contract_fp64(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld,
                           int64_t b0, int64_t nb, const double *nodes, const double *W, double *Y,
                           hipStream_t s, int variant);

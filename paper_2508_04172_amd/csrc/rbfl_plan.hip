@@ -32,7 +32,7 @@ struct Plan {
   int64_t total_items = 0;
   int grid = 0;
   int variant = 0;              // FP64 tile variant; -1 for the split form
-  int small = 0;                // small-batch tile in place of a rows + GEMM variant's (small_tile)
+  int small = 0;                // small-batch tile in place of a rows + GEMM variant's (ragged_small_tile)
   double tune_ms[8] = {};
   // split form (RBFL_PLAN_SPLIT): digits per event (caller order), the digit
   // rows and row scales of every event, and the work lists of the events
@@ -112,14 +112,15 @@ static void debug_check_plan(const Plan &p, const std::vector<EventDesc> &d,
 // columns, so the events go in decreasing row count: the longest items start
 // first and the last ones to finish are short (12 events of
 // 200 to 1500 nodes: 464 to 401 us at 1000 proposals each, 789 to 737 us at 2000,
-// against the order of decreasing proposals x rows x columns).
-static void plan_layout(Plan &p, int v, hipStream_t s) {
+// against the order of decreasing proposals x rows x columns).  pinned: the
+// variant's own tile whatever the batch size.
+static void plan_layout(Plan &p, int v, hipStream_t s, bool pinned = false) {
   int qt, cw;
   ragged_tile(v, &qt, &cw);
   const int n_ev = (int)p.ctx.size();
   // a small batch takes smaller tiles in place of the variant's (the same bits)
   p.small = 0;
-  if (v >= ragged_fused_variants()) {
+  if (v >= ragged_fused_variants() && !pinned) {
     int64_t tiles = 0;
     for (int e = 0; e < n_ev; ++e) tiles += (p.counts[e] + 31) / 32 * col_tiles(p.ctx[e]->host_consts, 32);
     p.small = ragged_small_tile(tiles);
@@ -437,8 +438,14 @@ static rbfl_plan_ctx *plan_create(const rbfl_handle *hs, int n_ev, const int64_t
     RBFL_HIP(hipEventCreate(&e1));
     int best = 0;
     double best_ms = 1e300;
-    for (int v = 0; v < ragged_variants() && v < 8; ++v) {
-      plan_layout(p, v, s);
+    // where the batch takes a small tile in place of the rows + GEMM variants',
+    // these are timed with their own tiles all the same, but what it does run
+    // (one more candidate) is what stands against the fused variants
+    const int nv = ragged_variants(), tiles = ragged_fused_variants();
+    plan_layout(p, tiles, s);
+    const bool small = p.small != 0;
+    for (int v = 0; v < nv + (small ? 1 : 0); ++v) {
+      plan_layout(p, v < nv ? v : tiles, s, v < nv);
       plan_run(p, s);
       double t[3];
       for (int r = 0; r < 3; ++r) {
@@ -451,10 +458,11 @@ static rbfl_plan_ctx *plan_create(const rbfl_handle *hs, int n_ev, const int64_t
         t[r] = ms;
       }
       std::sort(t, t + 3);
-      p.tune_ms[v] = t[1];
+      if (v < nv) p.tune_ms[v] = t[1];
+      if (small && v >= tiles && v < nv) continue;
       if (t[1] < best_ms) {
         best_ms = t[1];
-        best = v;
+        best = v < nv ? v : tiles;
       }
     }
     (void)hipEventDestroy(e0);

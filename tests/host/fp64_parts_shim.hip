@@ -11,7 +11,7 @@ void fp_parts(int K, int Kp, long long nb, int variant, long long *out) {
   EvalConsts hc{};
   hc.K = K;
   hc.Kp = Kp;
-  const Fp64Parts p = fp64_parts(hc, nb, variant);
+  const Fp64Parts p = fp64_parts(hc, nb, variant, false);
   const long long v[6] = {p.main.first, p.main.count, p.main.read_end, p.rest.first, p.rest.count, p.rest.read_end};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
