@@ -19,20 +19,23 @@ namespace rbfl {
 // the rest): one partial sum per proposal and column tile of the narrower of
 // the two tiles.
 static void reserve_lnl_gemm(Ctx &c, int64_t n) {
-  c.epi_su.alloc(epi_setup_bytes() * (size_t)n);
+  c.epi_su.reset();        // epi_su.p says that both are there
   c.epi_part.alloc((size_t)(c.Kp / std::min(gemm_lnl_col_tile(), split_col_tile())) * n);
+  c.epi_su.alloc(epi_setup_bytes() * (size_t)n);
 }
 
 void reserve(Ctx &c, int64_t n) {
   if (n <= c.cap) return;
   if (c.graph_users > 0) throw Error(RBFL_E_STATE, "the work space is captured by a sampler: it cannot grow");
+  // growing frees a buffer first: where that fails, no capacity is left that
+  // later calls could take for granted
+  c.cap = 0;
+  c.small_su = nullptr;
   c.Y.alloc((size_t)n * c.Kp);
   const size_t rows = (size_t)c.rows * rows_ld(n);
-  c.small_su = nullptr;
   c.Bt.alloc(rows + epi_setup_bytes() / sizeof(double) * (size_t)std::min<int64_t>(n, kSetupMax));
   c.small_su = c.Bt.p + rows;
   if (c.epi_su.p) reserve_lnl_gemm(c, n);
-  c.cap = n;
   if (c.prepared[RBFL_FORM_BF16]) c.A16.alloc((size_t)c.rows * n);
   if (c.prepared[RBFL_FORM_SPLIT]) {
     c.AS.alloc((size_t)split_max_slices() * n * c.rows);
@@ -43,6 +46,7 @@ void reserve(Ctx &c, int64_t n) {
     if (c.sur_nbase) c.sur_U.alloc((size_t)n * c.sur_nbase);
     c.sur->reserve(n);
   }
+  c.cap = n;
 }
 
 static bool contract(Ctx &c, const double *params, int64_t ld, int64_t b0, int64_t nb, int form, hipStream_t s,

@@ -1,0 +1,42 @@
+"""A work space that cannot grow: the call fails with RBFL_E_OUT_OF_MEMORY and the
+handle works as before, in every form whose buffers the failed growth touched."""
+import pytest
+
+from paper_2508_04172_amd import rbfl
+from paper_2508_04172_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+# 2^40 proposals: the first buffer of a petabyte.  2^25: the outputs fit (34 GB of
+# 128 columns), the basis rows do not (1216 or more rows: 326 GB of 288)
+@pytest.mark.parametrize("n_big", [1 << 40, 1 << 25])
+def test_failed_growth_leaves_a_working_handle(n_big):
+    import torch
+    cfg = wl.CFG1.with_(name="reserve", seg_len=8.0, n_nodes=1250, q=12, eps=0.0)
+    h = rbfl.Handle.from_config(cfg, wl.white_noise(cfg), wl.injection_extrinsics(cfg))
+    n = 500
+    idx, jit = wl.node_jitter(n, cfg.n_nodes)
+    qd = wl.queries(cfg, n=n).near_nodes(h.nodes(), idx, jit)
+    p = torch.from_numpy(rbfl.params_soa(h, qd, cfg.t_trig)).cuda()
+    stream = torch.cuda.current_stream().cuda_stream
+    for form in (rbfl.FORM_BF16, rbfl.FORM_SPLIT):
+        h.prepare(form)
+
+    def results():
+        out = []
+        for fused in (False, True):
+            h.fuse_epilogue(fused, split=fused)
+            for form in (rbfl.FORM_FP64, rbfl.FORM_BF16, rbfl.FORM_SPLIT):
+                l = torch.empty(n, device="cuda", dtype=torch.float64)
+                h.eval(p.data_ptr(), n, l.data_ptr(), form, stream)
+                out.append(l)
+        h.fuse_epilogue(False)
+        return torch.stack(out).cpu()
+
+    before = results()
+    torch.cuda.empty_cache()
+    with pytest.raises(rbfl.RbflError) as e:
+        h.reserve(n_big)
+    assert e.value.code == rbfl.E_OUT_OF_MEMORY
+    assert torch.equal(results().nan_to_num(7.0), before.nan_to_num(7.0))
