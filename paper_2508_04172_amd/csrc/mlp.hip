@@ -529,6 +529,7 @@ void Mlp::init(int n_in, int hidden, int n_out, const double *normals) {
 
 void Mlp::reserve(int64_t B) {
   if (B <= cap) return;
+  cap = 0;                 // a failed growth leaves no capacity behind
   Z1.alloc((size_t)B * hid);
   H1.alloc((size_t)B * hid);
   Z2.alloc((size_t)B * hid);
@@ -546,6 +547,7 @@ void Mlp::reserve(int64_t B) {
 void Mlp::reserve_grad(int64_t B) {
   reserve(B);
   if (B <= grad_cap) return;
+  grad_cap = 0;
   part.alloc((size_t)std::max<int64_t>(2048, (B + 63) / 64 * ((out + 63) / 64)));
   if (in <= kMaxIn1) part1.alloc((size_t)((B + 31) / 32) * hid * (in + 1));
   grad_cap = B;

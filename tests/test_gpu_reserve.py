@@ -1,5 +1,7 @@
 """A work space that cannot grow: the call fails with RBFL_E_OUT_OF_MEMORY and the
-handle works as before, in every form whose buffers the failed growth touched."""
+handle (or network) works as before, in every form whose buffers the failed
+growth touched."""
+import numpy as np
 import pytest
 
 from paper_2508_04172_amd import rbfl
@@ -40,3 +42,33 @@ def test_failed_growth_leaves_a_working_handle(n_big):
         h.reserve(n_big)
     assert e.value.code == rbfl.E_OUT_OF_MEMORY
     assert torch.equal(results().nan_to_num(7.0), before.nan_to_num(7.0))
+
+
+def test_failed_growth_leaves_a_working_network():
+    import torch
+    n_in, hidden, n_out, b = 4, 8, 65536, 64
+    m = rbfl.Mlp(n_in, hidden, n_out, wl.mlp_normals(rbfl.mlp_param_count(n_in, hidden, n_out), 3))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.rand(b, n_in, device="cuda", generator=gen)
+    t = torch.rand(b, n_out, device="cuda", generator=gen)
+    y = torch.empty(b, n_out, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def results():
+        m.forward(x.data_ptr(), b, y.data_ptr(), stream)
+        loss = m.loss_grad(x.data_ptr(), t.data_ptr(), b, stream)
+        return y.cpu(), loss, m.get(1)
+
+    before = results()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    filler = torch.empty(free - (12 << 30), dtype=torch.uint8, device="cuda")
+    # 65536 samples: 17 GB of outputs, where at most 12 are left; refused before
+    # any kernel reads the (too small) inputs
+    with pytest.raises(rbfl.RbflError) as e:
+        m.loss_grad(x.data_ptr(), t.data_ptr(), 65536, stream)
+    assert e.value.code == rbfl.E_OUT_OF_MEMORY
+    del filler
+    torch.cuda.empty_cache()
+    after = results()
+    assert torch.equal(before[0], after[0]) and before[1] == after[1] and np.array_equal(before[2], after[2])
