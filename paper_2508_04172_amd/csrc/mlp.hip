@@ -182,7 +182,9 @@ struct ProductLds {
 // bytes is four consecutive k of one row, so MFMA step s of a 16-deep group
 // multiplies k = s, 4 + s, 8 + s, 12 + s of it.  The next D chunks of 32 k
 // are in flight in registers; the k past the last full chunk are loaded first,
-// zeroed beyond the operand, and multiplied last.
+// zeroed beyond the operand, and multiplied last (up to 16 of them as one group:
+// 65,536 rows of 8 terms and 1275 outputs, bound by latency, 124 to 108 us for the
+// forward pass).
 template <int T, bool AK, bool BK, bool VEC>
 __device__ __forceinline__ void product_tile(const Product &p, int tile, ProductLds<T> &lds) {
   constexpr int TM = 32 * T;
@@ -226,6 +228,10 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
     const int64_t step = k_major ? 1 : ld;
     const float *q = P + 32 * n_full * step;
     f4 v;
+    if (k_major && VEC) {                // K % 4 == 0: a quad is whole or beyond the end
+      v = *reinterpret_cast<const f4 *>(k < tail ? q : q - k);
+      return k < tail ? v : f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const bool in = k + j < tail;
@@ -265,9 +271,10 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int u = 0; u < T; ++u) acc[h][t][u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  auto multiply = [&](int buf) {
+  auto multiply = [&](int buf, int halves = 2) {    // groups of 16 k of the chunk
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
+      if (h >= halves) break;
       f4 a[T], b[T];
 #pragma unroll
       for (int t = 0; t < T; ++t)
@@ -320,7 +327,7 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
     stash(0, ta, tb);
     add_columns(ta);
     __syncthreads();
-    multiply(0);
+    multiply(0, tail <= 16 ? 1 : 2);
     __syncthreads();
   }
   if (!AK && p.colsum != nullptr && tn == 0) {
@@ -336,6 +343,13 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
     }
     __syncthreads();
   }
+  // a tile's columns' biases ahead of the stores, which the compiler has to keep
+  // them behind otherwise: one load after another for each of the outputs
+  const bool biased = p.epi <= kLoss && p.bias != nullptr;
+  float bias[T] = {};
+  if (biased)
+#pragma unroll
+    for (int u = 0; u < T; ++u) bias[u] = p.bias[min(n0 + wc * 16 * T + 16 * u + ll, p.N - 1)];
   double sq = 0.0;
   float *ds = &lds.A[0][0][0];           // kLayer1Back: dZ1 of the tile, [TM][TM + 1]
   static_assert(sizeof(ProductLds<T>) >= sizeof(float) * (32 * T) * (32 * T + 1), "the tile fits the chunks' LDS");
@@ -350,7 +364,7 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
         const bool in = m < p.M && n < p.N;
         const int64_t at = (int64_t)m * p.N + n;
         float v = acc[0][t][u][i] + acc[1][t][u][i];
-        if (p.epi <= kLoss && p.bias && in) v += p.bias[n];
+        if (biased) v += bias[u];
         if (p.epi == kLinear) {
           if (in) p.C[at] = v;
         } else if (p.epi == kSilu) {
@@ -391,7 +405,11 @@ __device__ __forceinline__ void product_tile(const Product &p, int tile, Product
 template <int T, bool AK, bool BK, bool VEC>
 __global__ void __launch_bounds__(kT) k_product(Product p) {
   __shared__ ProductLds<T> lds;
-  product_tile<T, AK, BK, VEC>(p, blockIdx.x, lds);
+  // workgroups are dealt to the 8 XCDs in turn: a contiguous range of tiles on
+  // each, so that the column tiles of a row tile share an XCD's L2 (65,536 rows of
+  // 40 terms and 1275 outputs: 209 to 188 us for the whole forward pass)
+  const int64_t nblk = gridDim.x, bx = blockIdx.x, xcd = bx & 7, base = nblk >> 3, extra = nblk & 7;
+  product_tile<T, AK, BK, VEC>(p, (int)(xcd * base + (xcd < extra ? xcd : extra) + (bx >> 3)), lds);
 }
 
 // Two products of one stage of the backward pass in one launch: workgroups
@@ -413,24 +431,27 @@ __global__ void __launch_bounds__(kT) k_product_pair(Product w, Product x, int n
 // silu(Z).  A thread keeps one output's weights and goes through the rows
 // blockIdx.x R .. + R - 1 (every `par`-th, where the block holds several rows of
 // few outputs), so that it is bound by the stores: 65,536 rows of 256 outputs
-// 28 us, 100 with one output per thread and its index divided out.
-__global__ void __launch_bounds__(kT) k_layer1(const float *__restrict__ X, int B, int n_in, int hid, int R, int par,
+// 17.6 us, 100 with one output per thread and its index divided out, 26 with the
+// input count a variable, whose loads wait one for the other (64 outputs: 12.2
+// and 15).
+template <int IN>
+__global__ void __launch_bounds__(kT) k_layer1(const float *__restrict__ X, int B, int hid, int R, int par,
                                                const float *__restrict__ W1, const float *__restrict__ b1,
                                                float *__restrict__ Z, float *__restrict__ H) {
   const int sub = par > 1 ? (int)threadIdx.x / hid : 0;
   const int h = (int)(blockIdx.y * kT + threadIdx.x) - sub * hid;
   if (h >= hid || sub >= par) return;
-  float w[kMaxIn1];
+  float w[IN];
 #pragma unroll
-  for (int i = 0; i < kMaxIn1; ++i) w[i] = i < n_in ? W1[(int64_t)h * n_in + i] : 0.0f;
+  for (int i = 0; i < IN; ++i) w[i] = W1[(int64_t)h * IN + i];
   const float bias = b1[h];
   const int end = min(B, ((int)blockIdx.x + 1) * R);
+#pragma unroll 8
   for (int b = blockIdx.x * R + sub; b < end; b += par) {
-    const float *x = X + (int64_t)b * n_in;
+    const float *x = X + (int64_t)b * IN;
     float v = 0.0f;
 #pragma unroll
-    for (int i = 0; i < kMaxIn1; ++i)
-      if (i < n_in) v = fmaf(x[i], w[i], v);
+    for (int i = 0; i < IN; ++i) v = fmaf(x[i], w[i], v);
     v += bias;
     const int64_t e = (int64_t)b * hid + h;
     if (Z) Z[e] = v;
@@ -668,8 +689,20 @@ static void layer1(const Mlp &m, const float *X, int B, float *Z1, float *H1, hi
   // in turn to leave eight workgroups per CU
   const int par = std::max(1, kT / m.hid), cols = (m.hid + kT - 1) / kT;
   const int R = std::max(1, B * cols / (2048 * par)) * par;
-  hipLaunchKernelGGL(k_layer1, dim3((B + R - 1) / R, cols), dim3(kT), 0, s, X, B, m.in, m.hid, R, par,
-                     m.p.p + m.o_w1, m.p.p + m.o_b1, Z1, H1);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((B + R - 1) / R, cols), dim3(kT), 0, s, X, B, m.hid, R, par, m.p.p + m.o_w1,
+                       m.p.p + m.o_b1, Z1, H1);
+  };
+  static_assert(kMaxIn1 == 7, "one kernel per input count");
+  switch (m.in) {
+    case 1: launch(k_layer1<1>); break;
+    case 2: launch(k_layer1<2>); break;
+    case 3: launch(k_layer1<3>); break;
+    case 4: launch(k_layer1<4>); break;
+    case 5: launch(k_layer1<5>); break;
+    case 6: launch(k_layer1<6>); break;
+    default: launch(k_layer1<7>);
+  }
   RBFL_HIP(hipGetLastError());
 }
 
