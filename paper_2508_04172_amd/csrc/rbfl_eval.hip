@@ -168,7 +168,6 @@ static void eval_lnl_gemm(Ctx &c, const double *params, int64_t ld, int64_t n, d
 
 // The split form with ln L finished inside its contraction, chunk by chunk.
 static void eval_split_lnl(Ctx &c, const double *params, int64_t ld, int64_t n, double *lnl, hipStream_t s) {
-  const int n_ct = col_tiles(c.host_consts, split_col_tile());
   if (!c.epi_su.p) {
     if (capturing(s)) throw Error(RBFL_E_STATE, "work space of the fused epilogue not allocated (evaluate once before capture)");
     reserve_lnl_gemm(c, c.cap);
@@ -187,7 +186,7 @@ static void eval_split_lnl(Ctx &c, const double *params, int64_t ld, int64_t n, 
                      c.WSscale.p, c.epi_su.p, c.basis4.p, c.coldesc.p, c.epi_part.p, c.cap, s,
                      c.variant[RBFL_FORM_SPLIT], c.profile ? ev[1] : nullptr);
     if (c.profile) RBFL_HIP(hipEventRecord(ev[2], s));
-    launch_lnl_tiles(c.epi_su.p, b0, nb, c.epi_part.p, c.cap, n_ct, lnl, s);
+    launch_lnl_tiles(c.epi_su.p, b0, nb, c.epi_part.p, c.cap, split_lnl_col_tiles(c.host_consts, nb), lnl, s);
     if (c.profile) {
       RBFL_HIP(hipEventRecord(ev[3], s));
       // stages: setups + digit rows (kind 2), contraction with the weighting

@@ -456,6 +456,7 @@ bool launch_contract_split(const EvalConsts *c, const EvalConsts &hc, const doub
 // tile into part[tile][ldp] from the setups of launch_epi_setup; mid, when
 // given, is recorded between the two.
 int split_col_tile();
+int split_lnl_col_tiles(const EvalConsts &hc, int64_t nb);   // column tiles of that contraction of nb proposals
 void launch_split_lnl(const EvalConsts *c, const EvalConsts &hc, const double *params, int64_t ld, int64_t b0,
                       int64_t nb, const double *nodes, int8_t *AS, double *rscale, const int8_t *BS,
                       const double *cscale, const void *setups, const double2 *basis4, const int4 *coldesc,
