@@ -367,7 +367,7 @@ int32_t rbfl_query(rbfl_handle h, int32_t what, void *out, size_t bytes);
  * first min(n, work capacity) proposals of `params` (device [11][n]) with HIP
  * events on `stream` and keeps the fastest for this handle (RBFL_Q_TUNE
  * reports the timings).  FP64 tiles that evaluations of this batch do not run
- * (rbfl_set_variant) are timed but not kept: the handle keeps the tile it had,
+ * (rbfl_set_variant) are timed (one launch) but not kept: the handle keeps the tile it had,
  * unless the fused variant is faster than what the batch does run.  Split-form variants differ in digit count S (5..8,
  * variant v has S = 5 + v): only those whose ln L on these proposals stays
  * within the handle's split tolerance (rbfl_set_split_tol, default

@@ -407,13 +407,16 @@ void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) 
   if (by_size) run(nv);
   // two interleaved rounds of three timed launches per variant (so that no
   // variant is timed alone while the clocks settle); keep each variant's
-  // smaller round median
+  // smaller round median.  Tiles that this batch does not run are timed for
+  // their report alone: one launch.
   double med[9];
   for (double &m : med) m = 1e300;
   for (int round = 0; round < 2; ++round)
     for (int v = 0; v < nv + (by_size ? 1 : 0); ++v) {
+      const int reps = v == nv || runs[v] ? 3 : 1 - round;
+      if (reps == 0) continue;
       double t[3];
-      for (int r = 0; r < 3; ++r) {
+      for (int r = 0; r < reps; ++r) {
         RBFL_HIP(hipEventRecord(e0, s));
         run(v);
         RBFL_HIP(hipEventRecord(e1, s));
@@ -422,8 +425,8 @@ void autotune(Ctx &c, const double *params, int64_t n, int form, hipStream_t s) 
         RBFL_HIP(hipEventElapsedTime(&ms, e0, e1));
         t[r] = ms;
       }
-      std::sort(t, t + 3);
-      med[v] = std::min(med[v], t[1]);
+      std::sort(t, t + reps);
+      med[v] = std::min(med[v], t[reps / 2]);
     }
   for (int v = 0; v < nv && v < 8; ++v) {
     c.tune_ms[form][v] = med[v];

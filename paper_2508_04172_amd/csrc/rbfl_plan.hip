@@ -439,16 +439,18 @@ static rbfl_plan_ctx *plan_create(const rbfl_handle *hs, int n_ev, const int64_t
     int best = 0;
     double best_ms = 1e300;
     // where the batch takes a small tile in place of the rows + GEMM variants',
-    // these are timed with their own tiles all the same, but what it does run
-    // (one more candidate) is what stands against the fused variants
+    // these are timed with their own tiles all the same (one launch, for the
+    // report), but what it does run (one more candidate) is what stands against the
+    // fused variants
     const int nv = ragged_variants(), tiles = ragged_fused_variants();
     plan_layout(p, tiles, s);
     const bool small = p.small != 0;
     for (int v = 0; v < nv + (small ? 1 : 0); ++v) {
+      const int reps = small && v >= tiles && v < nv ? 1 : 3;
       plan_layout(p, v < nv ? v : tiles, s, v < nv);
       plan_run(p, s);
       double t[3];
-      for (int r = 0; r < 3; ++r) {
+      for (int r = 0; r < reps; ++r) {
         RBFL_HIP(hipEventRecord(e0, s));
         plan_run(p, s);
         RBFL_HIP(hipEventRecord(e1, s));
@@ -457,9 +459,9 @@ static rbfl_plan_ctx *plan_create(const rbfl_handle *hs, int n_ev, const int64_t
         RBFL_HIP(hipEventElapsedTime(&ms, e0, e1));
         t[r] = ms;
       }
-      std::sort(t, t + 3);
-      if (v < nv) p.tune_ms[v] = t[1];
-      if (small && v >= tiles && v < nv) continue;
+      std::sort(t, t + reps);
+      if (v < nv) p.tune_ms[v] = t[reps / 2];
+      if (reps == 1) continue;
       if (t[1] < best_ms) {
         best_ms = t[1];
         best = v < nv ? v : tiles;
