@@ -46,12 +46,14 @@ PROFILE = os.path.join(ROOT, "profiles", "k_gemm_fp64_cfg2_hlv_5mode.md")
 
 
 def gemm_source_hash() -> str:
-    """Hash of what fixes the FP64 GEMM's memory traffic: its source file and
-    the row and column padding of the library."""
+    """Hash of what fixes the FP64 GEMM's memory traffic: its source file, the
+    rules that deal a batch to its tiles, and the row and column padding of the
+    library."""
     import hashlib
     import re
     csrc = os.path.join(ROOT, "paper_2508_04172_amd", "csrc")
     h = hashlib.sha256(open(os.path.join(csrc, "contract_fp64.hip"), "rb").read())
+    h.update(open(os.path.join(csrc, "fp64_parts.h"), "rb").read())
     consts = open(os.path.join(csrc, "rbfl_internal.h")).read()
     for name in ("kRowChunk", "kColTile"):
         h.update(re.search(rf"constexpr int {name} = (\d+);", consts).group(0).encode())

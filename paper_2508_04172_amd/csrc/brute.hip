@@ -51,8 +51,8 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
 // time): rounded once each it left ln L of 300 proposals 5.0e-14 of its norm
 // from a plain 64-bit evaluation, as the sums per detector and mode were; now
 // 4.2e-14.  301 proposals of 32,448
-// bins, 5 modes, 3 detectors: 0.18 ms, 1.04 ms with the templates formed per
-// detector and 20 complex sums per thread.
+// bins, 5 modes, 3 detectors: 0.18-0.21 ms by the card's clock, 1.04-1.20 ms with
+// the templates formed per detector and 20 complex sums per thread.
 template <int ND, int BT>
 __global__ void __launch_bounds__(BT, 4) k_brute(const EvalConsts *__restrict__ cp, const double *__restrict__ params,
                                               int64_t ld, const double2 *__restrict__ Dd,

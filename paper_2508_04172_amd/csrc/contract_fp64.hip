@@ -1,21 +1,33 @@
-// FP64 form of the interpolant contraction Y = [Phi | P] W (Eq. rbfcoeff) as
-// two kernels: the basis rows of a chunk of proposals are written to HBM by a
-// VALU-only kernel, then a DGEMM-shaped FP64 MFMA kernel contracts them with
-// the weights.
+// FP64 form of the interpolant contraction Y = [Phi | P] W (Eq. rbfcoeff).  All
+// kernels add the rows in one order with one MFMA, so the outputs do not depend on
+// which of them a batch takes; fp64_parts.h holds the rules on sizes.
 //
-// Why not fused: on gfx950 an FP64 MFMA and any VALU instruction of the same
-// SIMD do not execute concurrently (the co-execution counter stays at zero),
-// so the ~45 VALU instructions of each fused exp(-eps^2 d^2) row value (plus
-// its recomputation for every column tile) are added to the MFMA time.  Apart
-// from the rows the GEMM's inner loop issues only LDS reads and MFMAs; the
-// rows cost one HBM round trip of 8 (N + M) bytes per proposal.
+// Large batches, and the base of the others: the basis rows of a chunk of
+// proposals are written to HBM by a VALU-only kernel (k_rows_fp64; small batches
+// k_rows_small_fp64 or, with the epilogue's setups, k_rows_setup_fp64; plans
+// k_ragged_rows_fp64), then a DGEMM-shaped FP64 MFMA kernel contracts them with
+// the weights:
+//   k_gemm_fp64            the handle's tile variant; 64 x 64 in batches of the
+//                          middle sizes and for a short last round
+//   k_gemm_small_fp64      32 x 32 tiles, four chunks in flight, small batches
+//   k_gemm_lnl_fp64        128 x 128 tiles that finish ln L themselves
+//   k_ragged_gemm_*        the same tiles over a plan's work list
+// Why rows and product are two kernels: on gfx950 an FP64 MFMA and any VALU
+// instruction of the same SIMD do not execute concurrently (the co-execution
+// counter stays at zero), so the ~45 VALU instructions of each fused
+// exp(-eps^2 d^2) row value (plus its recomputation for every column tile) are
+// added to the MFMA time.  Apart from the rows the GEMM's inner loop issues only
+// LDS reads and MFMAs; the rows cost one HBM round trip of 8 (N + M) bytes per
+// proposal.
+//   k_rows_gemm_fp64       is the exception: with one column tile every row value
+//                          is used by one workgroup only, which forms it in LDS
 //
 // Layouts: rows Bt[r][q] (row r of proposal q, leading dimension ldb, a
 // multiple of 8 >= nb, zero beyond nb); weights W[r][c] (Kp columns).
-// GEMM tiles: 4 waves (2 x 2), each RT x CT tiles of 16 x 16 on
-// v_mfma_f64_16x16x4f64 (lane l holds A[l%16][l/16], B[l/16][l%16];
-// accumulator element i is D[l/16 + 4i][l%16], measured on gfx950); row
-// chunks of KC rows of both operands staged through LDS, double-buffered.
+// v_mfma_f64_16x16x4f64 (lane l holds A[l%16][l/16], B[l/16][l%16]; accumulator
+// element i is D[l/16 + 4i][l%16], measured on gfx950); a tile's WQ x WC waves
+// hold RT x CT tiles of 16 x 16 each; chunks of KC rows of both operands are
+// staged through LDS, double-buffered.
 #include "basis_rows.h"
 #include "epilogue_setup.h"
 #include "fp64_parts.h"

@@ -517,9 +517,9 @@ __global__ void __launch_bounds__(kThreads) k_series_lnl(const EvalConsts *__res
 // ---- multi-event (ragged) batch --------------------------------------------
 
 // Persistent contraction over the work list of every event: items are
-// (event, proposal tile, column tile), numbered event by event in the
-// caller's order; each block takes the next item from an atomic counter
-// until the list is exhausted (every block reaches that exit).
+// (event, proposal tile, column tile), numbered event by event in decreasing
+// row count; each block takes the next item from an atomic counter until the
+// list is exhausted (every block reaches that exit).
 template <int RT, int CT, int CH>
 __global__ void __launch_bounds__(kThreads) k_ragged_contract_fp64(const EventDesc *__restrict__ ev, int n_ev,
                                                                    int64_t total_items,
