@@ -35,10 +35,11 @@ def test_small_batch_keeps_the_tile(before):
     h, p = setup(cfg, n)
     h.reserve(n)
     h.set_variant(rbfl.FORM_FP64, before)
-    tune = h.autotune(p.data_ptr(), n, rbfl.FORM_FP64, stream())
-    print(f"[autotune] {n} proposals, tile {before} before: {tune}", flush=True)
-    assert tune["variant"] == before and len(tune["ms"]) == rbfl_variants()
-    assert tune["ms"][5] >= 1.5 * tune["ms"][4]
+    tunes = [h.autotune(p.data_ptr(), n, rbfl.FORM_FP64, stream()) for _ in range(3)]
+    print(f"[autotune] {n} proposals, tile {before} before: {tunes[0]}", flush=True)
+    assert all(t["variant"] == before and len(t["ms"]) == rbfl_variants() for t in tunes)
+    best = np.min([t["ms"] for t in tunes], axis=0)   # one launch each: the least disturbed
+    assert best[5] >= 1.5 * best[4]
 
 
 def rbfl_variants():
