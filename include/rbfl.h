@@ -296,7 +296,9 @@ int32_t rbfl_interp(rbfl_handle h, const double *params, int64_t n, double *out,
  * form this library or this handle's size does not support. */
 int32_t rbfl_prepare(rbfl_handle h, int32_t form);
 
-/* Pre-allocates work space for batches of up to n proposals (optional). */
+/* Pre-allocates work space for batches of up to n proposals (optional).  Where
+ * it does not fit (RBFL_E_OUT_OF_MEMORY) the handle is left without one; the
+ * next evaluation allocates its own. */
 int32_t rbfl_reserve(rbfl_handle h, int64_t n);
 
 /* Artefact export (host copies), for checks and diagnostics. */
